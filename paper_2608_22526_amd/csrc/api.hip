@@ -543,9 +543,11 @@ rs3_status rs3_select_workspace_size(const rs3_grid* g, int32_t n_obj, int64_t x
   const int64_t mn = (int64_t)g->m * g->n;
   const int n_x = x_obj_stride ? n_obj : 1;
   // energies [n_x][mn] fp64, per-64-cell energy ranges [n_x][ceil(mn/64)][2],
-  // then the priors computed beside the energies [n_obj][64][4] u64
+  // then what is computed beside the energies: the priors [n_obj][64][4] u64,
+  // or the mask rows' bits [n_obj][m][4] u64 and boxes [n_obj][m][4] i32
+  const size_t rows = (size_t)n_obj * g->m * (32 + 16), priors = (size_t)n_obj * 64 * 4 * 8;
   *bytes = align256((size_t)n_x * mn * 8) + align256((size_t)n_x * ((mn + 63) / 64) * 16) +
-           (size_t)n_obj * 64 * 4 * 8;
+           (rs3_select_prior_beside(g->m, g->n, g->s) ? priors : rows > priors ? rows : priors);
   return RS3_OK;
 }
 
@@ -612,18 +614,19 @@ static rs3_status select_args(const rs3_grid* g, int32_t n_obj, const uint8_t* m
   return RS3_OK;
 }
 
-// Energies (and the priors beside them, and with qp every row's projected
-// query), then the selection.
+// Energies (beside them the priors or the scan of the mask rows, and with qp
+// every row's projected query), then the selection.
 static hipError_t select_launch(SelectLaunch& sl, hipStream_t st, const Rs3QProjArgs* qp = nullptr) {
   Rs3SelectArgs& a = sl.a;
   hipError_t he;
   if (rs3_select_prior_beside(a.m, a.n, a.s)) {
     a.prior_bits = sl.pbits;
-    he = rs3_launch_energy_prior(sl.X, sl.x_stride, sl.n_x, sl.mn, sl.C, sl.dtype, sl.e, sl.erange, a, sl.n_groups, st,
-                                 qp);
   } else {
-    he = rs3_launch_energy(sl.X, sl.x_stride, sl.n_x, sl.mn, sl.C, sl.dtype, sl.e, sl.erange, st, qp);
+    a.row_bits = sl.pbits;
+    a.row_box = (int32_t*)(sl.pbits + (size_t)a.n_obj * a.m * 4);
   }
+  he = rs3_launch_energy_prior(sl.X, sl.x_stride, sl.n_x, sl.mn, sl.C, sl.dtype, sl.e, sl.erange, a, sl.n_groups, st,
+                               qp);
   if (he != hipSuccess) return he;
   return rs3_launch_select(a, sl.n_groups, st);
 }

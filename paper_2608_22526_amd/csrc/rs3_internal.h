@@ -166,6 +166,8 @@ struct Rs3SelectArgs {
   int32_t* sel_count;     // [n_groups]
   uint8_t* prior_out;     // [n_groups][mn] or null
   uint64_t* prior_bits;   // [n_groups][64][4] prior rows computed beside the energies, or null
+  uint64_t* row_bits;     // [n_obj][m][4] down-sampled mask rows scanned beside the energies, or null
+  int32_t* row_box;       // [n_obj][m][4] pixel box (y0, x0, y1, x1) of each grid row, or null (then prior_bits)
   int m, n, s, n_obj, union_objects, seed_box, r_s, c, x_per_obj;
   int k[RS3_MAX_OBJ];
 };
@@ -296,15 +298,12 @@ struct StkArgs {
 };
 
 // Launchers (all enqueue on `st` and return the launch status).
-// qp (optional, bf16 grids of 256 channels only): the launch also projects
-// every row (Rs3QProjArgs).
-hipError_t rs3_launch_energy(const void* X, int64_t x_stride, int n_x, int mn, int C, int dtype,
-                             double* e, unsigned long long* range, hipStream_t st,
-                             const Rs3QProjArgs* qp = nullptr);
 hipError_t rs3_launch_select(const Rs3SelectArgs& a, int n_groups, hipStream_t st);
 // Grids for which the prior runs beside the energies (one wave per group).
 bool rs3_select_prior_beside(int m, int n, int s);
-// Energies and the one-wave priors (written to a.prior_bits) in one launch.
+// Energies and, in the same launch, the one-wave priors (a.prior_bits) or the
+// scan of the mask rows (a.row_box).  qp (optional, bf16 grids of 256
+// channels only): the launch also projects every row (Rs3QProjArgs).
 hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int mn, int C, int dtype, double* e,
                                    unsigned long long* range, const Rs3SelectArgs& a, int n_groups, hipStream_t st,
                                    const Rs3QProjArgs* qp = nullptr);

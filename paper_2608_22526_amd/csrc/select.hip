@@ -1,9 +1,11 @@
 // Read-side keep-set: spatial prior (Sec. 3.1, Eqs. 1, 2, 5; tracker update
 // of Algorithm 1) and the energy top-k inside it (Eq. 4).
 //
-// k_energy : e_i = sum_c x_{i,c}^2 in fp64, channels added in ascending
+// k_energy_prior : e_i = sum_c x_{i,c}^2 in fp64, channels added in ascending
 //            order, one lane per token row (the squares of bf16/fp32 values
-//            are exact in fp64, so the sums are reproducible bit for bit).
+//            are exact in fp64, so the sums are reproducible bit for bit),
+//            and beside them the priors of small grids or the scan of the
+//            mask rows.
 // k_select : one 1024-thread workgroup per group.  Builds the group's prior
 //            bitmap in LDS (per-object bbox, streak update, separable
 //            Chebyshev dilation), then finds the k-th largest energy with an
@@ -225,51 +227,35 @@ __device__ __forceinline__ void energy_block_wide(const T* __restrict__ X, int64
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_energy_wide(const T* __restrict__ X, int64_t x_stride, int mn, int C,
-                                                     double* __restrict__ e, unsigned long long* __restrict__ range) {
-  energy_block_wide<T>(X, x_stride, mn, C, e, range, blockIdx.x, blockIdx.y);
-}
-
-template <typename T, bool QP = false>
-__global__ __launch_bounds__(256) void k_energy(const T* __restrict__ X, int64_t x_stride, int mn,
-                                                 int C, double* __restrict__ e,
-                                                 unsigned long long* __restrict__ range, Rs3QProjArgs qp) {
-  energy_block<T, QP>(X, x_stride, mn, C, e, range, blockIdx.x, blockIdx.y, gridDim.x, &qp);
-}
-
-
 // ---------------------------------------------------------------------------
 // block-wide helpers for a 1024-thread workgroup
 struct SelShared {
   int red[SEL_WAVES];
   unsigned long long redu[SEL_WAVES];
-  int bb[4];
-  int mode, r, gy0, gx0, gy1, gx1;
+  // prior of each object: mode, radius and grid box (row and column, inclusive)
+  int mode[RS3_MAX_OBJ], rad[RS3_MAX_OBJ], gy0[RS3_MAX_OBJ], gx0[RS3_MAX_OBJ], gy1[RS3_MAX_OBJ], gx1[RS3_MAX_OBJ];
   int hist[256];
   int digit, remaining, full;
   int ncand;
   int red1[SEL_WAVES], red2[SEL_WAVES], red3[SEL_WAVES];
-  unsigned long long rowbits[SEL_WAVES];   // rows with a set cell, one bit per row
-  unsigned long long colbits[4];           // columns with a set cell
   unsigned long long kmin, kmax;
 };
 
-// Exclusive prefix (in thread order) of the number of set bits among the
-// first cpt bits of `bits`, and the workgroup total; `red` is a private
-// SEL_WAVES-entry LDS array of the call site.  Ballot-based: no LDS or
-// cross-lane permutes inside a wave.
+// Cells of a thread: wave w owns the 64*cpt cells from 64*cpt*w, lane l of it
+// the cells l, l + 64, ... of those, so that a wave reads 64 consecutive
+// energies per load (with cpt consecutive cells per thread each load touched
+// 64 cache lines: 40.2 us against 30.0 us per selection of a 128x128 grid).
+//
+// Number of set bits before this wave's cells (bits j < cpt of every thread,
+// in cell order), and the workgroup total; `red` is a private
+// SEL_WAVES-entry LDS array of the call site.
 template <int MAXC>
 __device__ __forceinline__ int block_scan_bits(uint32_t bits, int cpt, int* red, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int pre = 0, wtot = 0;
+  int wtot = 0;
 #pragma unroll
   for (int j = 0; j < MAXC; ++j)
-    if (j < cpt) {
-      const unsigned long long b = __ballot((bits >> j) & 1u);
-      pre += __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-      wtot += __popcll(b);
-    }
+    if (j < cpt) wtot += __popcll(__ballot((bits >> j) & 1u));
   if (lane == 0) red[wave] = wtot;
   lds_barrier();
   int before = 0, tot = 0;
@@ -280,40 +266,12 @@ __device__ __forceinline__ int block_scan_bits(uint32_t bits, int cpt, int* red,
     before += w < wave ? v : 0;
   }
   *total = tot;
-  return before + pre;
+  return before;
 }
 
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    int t = __shfl_up(v, off, 64);
-    if (lane >= off) v += t;
-  }
-  return v;
-}
-
-// Exclusive prefix over the workgroup in thread order; returns the prefix
-// and writes the total to *total.
-__device__ int block_excl_scan(int v, SelShared& sh, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = wave_incl_scan(v, lane);
-  if (lane == 63) sh.red[wave] = inc;
-  __syncthreads();
-  int wsum = 0, tot = 0;
-  for (int w = 0; w < SEL_WAVES; ++w) {
-    int s = sh.red[w];
-    if (w < wave) wsum += s;
-    tot += s;
-  }
-  __syncthreads();
-  *total = tot;
-  return wsum + inc - v;
-}
-
-__device__ int block_sum(int v, SelShared& sh) {
-  int tot;
-  block_excl_scan(v, sh, &tot);
-  return tot;
+// Set bits of `b` (one per lane) below this lane.
+__device__ __forceinline__ int bits_below(unsigned long long b) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
 }
 
 __device__ unsigned long long block_minmax_u64(unsigned long long v, bool want_max, SelShared& sh) {
@@ -391,15 +349,19 @@ __device__ __forceinline__ uint64_t last_word_mask(int n, int W, int w) {
   return (w == W - 1 && rem < 64) ? ((1ull << rem) - 1ull) : ~0ull;
 }
 
+// Grids of at most FAST_W*64 columns hold a row as FAST_W bit words.
+constexpr int FAST_W = 4;
+
 // Tracker update of object o (single thread) from the box of its set pixels
-// (y1 < 0: empty mask), on the LDS copy of its words; writes the words back
-// and publishes the prior mode, radius and grid box in sh.
-__device__ void tracker_update(const Rs3SelectArgs& a, int o, int* tl, int by0, int bx0, int by1, int bx1,
-                               SelShared& sh) {
+// (y1 < 0: empty mask); publishes the object's prior mode, radius and grid
+// box in sh.
+__device__ void tracker_update(const Rs3SelectArgs& a, int o, int by0, int bx0, int by1, int bx1, SelShared& sh) {
   int32_t* tr = a.track + o * RS3_TRACK_WORDS;
-  const bool nonempty = by1 >= 0;
+  int tl[RS3_TRACK_WORDS];
+#pragma unroll
+  for (int w = 0; w < RS3_TRACK_WORDS; ++w) tl[w] = tr[w];
   int mode = MODE_NONE, r = a.r_s;
-  if (nonempty) {
+  if (by1 >= 0) {
     mode = a.seed_box ? MODE_BOX : MODE_MASK;
     tl[0] = by0;
     tl[1] = bx0;
@@ -419,22 +381,120 @@ __device__ void tracker_update(const Rs3SelectArgs& a, int o, int* tl, int by0, 
       r = a.r_s + min(d, a.c);
     }
   }
+#pragma unroll
   for (int w = 0; w < RS3_TRACK_WORDS; ++w) tr[w] = tl[w];
-  sh.mode = mode;
-  sh.r = r;
   const int s = a.s;
   if (mode == MODE_NONE) by0 = bx0 = by1 = bx1 = 0;
-  sh.gy0 = s == 1 ? by0 : by0 / s;
-  sh.gx0 = s == 1 ? bx0 : bx0 / s;
-  sh.gy1 = s == 1 ? by1 : by1 / s;
-  sh.gx1 = s == 1 ? bx1 : bx1 / s;
+  sh.mode[o] = mode;
+  sh.rad[o] = r;
+  sh.gy0[o] = s == 1 ? by0 : by0 / s;
+  sh.gx0[o] = s == 1 ? bx0 : bx0 / s;
+  sh.gy1[o] = s == 1 ? by1 : by1 / s;
+  sh.gx1[o] = s == 1 ? bx1 : bx1 / s;
 }
 
-// Register path of the prior: grids of at most SEL_THREADS rows and
-// FAST_W*64 columns.  Thread y owns grid row y as FAST_W bit words; row
-// dilation is shifts inside the thread, the column dilation reads the
-// neighbouring rows once through LDS (rows: [m][FAST_W] words).
-constexpr int FAST_W = 4;
+// Boxes and tracker updates of the objects o0 .. o0+no-1, one wave each, from
+// the boxes of their grid rows (row_scan).  The caller's barrier publishes
+// the prior words in sh.
+__device__ __forceinline__ void objects_update(const Rs3SelectArgs& a, int o0, int no, SelShared& sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = o0 + wave; o < o0 + no; o += SEL_WAVES) {
+    const int4* rb = (const int4*)a.row_box + (int64_t)o * a.m;
+    int y0 = 0x7fffffff, x0 = 0x7fffffff, y1 = -1, x1 = -1;
+    for (int y = lane; y < a.m; y += 64) {
+      const int4 b = rb[y];
+      y0 = min(y0, b.x);
+      x0 = min(x0, b.y);
+      y1 = max(y1, b.z);
+      x1 = max(x1, b.w);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      y0 = min(y0, __shfl_xor(y0, off, 64));
+      x0 = min(x0, __shfl_xor(x0, off, 64));
+      y1 = max(y1, __shfl_xor(y1, off, 64));
+      x1 = max(x1, __shfl_xor(x1, off, 64));
+    }
+    if (lane == 0) tracker_update(a, o, y0, x0, y1, x1, sh);
+  }
+}
+
+// One wave: grid row y of object o, that is the pixel rows y*s .. y*s+s-1 of
+// its mask.  Writes the box of their set pixels (int4 y0, x0, y1, x1; empty:
+// 2^31-1, 2^31-1, -1, -1) to row_box and, for grids of at most FAST_W*64
+// columns, the row's down-sampled bits to row_bits.  The pixel rows are one
+// contiguous run of bytes, read once in 16-byte loads between its unaligned
+// ends: with one work-group per selection reading every byte the selection of
+// three 480x864 masks (1.2 MB) took 408 us; it takes 8.9 us since, and the
+// energy launch that holds these waves 8.0 instead of 5.2 us.
+__device__ __forceinline__ void row_scan(const Rs3SelectArgs& a, int o, int y) {
+  const int lane = threadIdx.x & 63;
+  const int n = a.n, s = a.s, Wpx = n * s, W = (n + 63) >> 6;
+  const int64_t len = (int64_t)s * Wpx;
+  const uint8_t* R = a.masks + ((int64_t)o * a.m + y) * len;
+  if (a.row_bits && W <= FAST_W) {
+    uint64_t* rw = a.row_bits + ((int64_t)o * a.m + y) * FAST_W;
+#pragma unroll
+    for (int q = 0; q < FAST_W; ++q) {
+      const int x = 64 * q + lane;
+      const uint64_t word = __ballot(x < n && R[(int64_t)min(x, n - 1) * s] != 0);
+      if (lane == 0) rw[q] = word;
+    }
+  }
+  int y0 = 0x7fffffff, x0 = 0x7fffffff, y1 = -1, x1 = -1;
+  auto add = [&](int64_t p) {   // set pixel at byte p of the run
+    const int r = (int)((uint32_t)p / (uint32_t)Wpx), x = (int)p - r * Wpx;
+    y0 = min(y0, r);
+    y1 = max(y1, r);
+    x0 = min(x0, x);
+    x1 = max(x1, x);
+  };
+  const int head = (int)min((int64_t)((16 - (uintptr_t)R) & 15), len);
+  const int64_t nvec = (len - head) >> 4, tail0 = head + 16 * nvec;
+  if (lane < head && R[lane]) add(lane);
+  if (lane < len - tail0 && R[tail0 + lane]) add(tail0 + lane);
+  for (int64_t v0 = lane; v0 < nvec; v0 += 256) {
+    u32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *(const u32x4*)(R + head + 16 * min(v0 + 64 * u, nvec - 1));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (v0 + 64 * u >= nvec || (v[u][0] | v[u][1] | v[u][2] | v[u][3]) == 0u) continue;
+      uint32_t bits = 0;   // one per set byte
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint32_t t = v[u][e];
+        t |= t >> 4;
+        t |= t >> 2;
+        t |= t >> 1;
+        bits |= ((t & 1u) | ((t >> 7) & 2u) | ((t >> 14) & 4u) | ((t >> 21) & 8u)) << (4 * e);
+      }
+      const int64_t p = head + 16 * (v0 + 64 * u);
+      // within one pixel row the first and the last set byte bound the rest
+      const int first = __builtin_ctz(bits), last = 31 - __builtin_clz(bits);
+      add(p + first);
+      add(p + last);
+      if (Wpx < 32 || (uint32_t)(p + first) / (uint32_t)Wpx != (uint32_t)(p + last) / (uint32_t)Wpx)
+        for (int e = first + 1; e < last; ++e)
+          if (bits >> e & 1u) add(p + e);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    y0 = min(y0, __shfl_xor(y0, off, 64));
+    x0 = min(x0, __shfl_xor(x0, off, 64));
+    y1 = max(y1, __shfl_xor(y1, off, 64));
+    x1 = max(x1, __shfl_xor(x1, off, 64));
+  }
+  if (lane == 0) {
+    int4 b;
+    b.x = y1 < 0 ? y0 : y * s + y0;
+    b.y = x0;
+    b.z = y1 < 0 ? y1 : y * s + y1;
+    b.w = x1;
+    ((int4*)a.row_box)[(int64_t)o * a.m + y] = b;
+  }
+}
 
 __device__ __forceinline__ void row_dilate_regs(uint64_t* w, int W, int n, int rr) {
   int done = 0;
@@ -459,144 +519,59 @@ __device__ __forceinline__ void row_dilate_regs(uint64_t* w, int W, int n, int r
   }
 }
 
-// Adds object o's prior to the group rows g[] of this thread's grid row.
-// Communication is through LDS only (lds_barrier).
-__device__ void add_object_prior_fast(const Rs3SelectArgs& a, int o, uint64_t* rows, uint64_t* g,
-                                      SelShared& sh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m = a.m, n = a.n, s = a.s, W = (n + 63) >> 6;
-  const int Wpx = n * s, Hpx = m * s;
-  const uint8_t* M = a.masks + (int64_t)o * Hpx * Wpx;
-  int tw[RS3_TRACK_WORDS];   // tracker words (thread 0), first used after the box
-  if (tid == 0)
-    for (int w = 0; w < RS3_TRACK_WORDS; ++w) tw[w] = a.track[o * RS3_TRACK_WORDS + w];
-  const int y = tid;
+// Prior of the objects o0 .. o0+no-1 as rows of bit words (grids of at most
+// SEL_THREADS rows and FAST_W*64 columns): thread y owns grid row y.  Objects
+// in mask mode share the radius r_s and dilation distributes over the union,
+// so their rows are joined first and dilated once: inside the row by shifts,
+// across rows through LDS (rows: [m][W] words).  sh holds the objects' prior
+// words (objects_update).  Ends with a barrier still to pass before `rows`
+// is rewritten.
+__device__ __forceinline__ void add_priors_fast(const Rs3SelectArgs& a, int o0, int no, uint64_t* rows, uint64_t* g,
+                                                SelShared& sh) {
+  const int y = threadIdx.x;
+  const int m = a.m, n = a.n, W = (n + 63) >> 6;
   uint64_t w[FAST_W] = {0, 0, 0, 0};
+  bool any_mask = false;
+  for (int o = o0; o < o0 + no; ++o) {
+    const int mode = sh.mode[o];
+    if (mode == MODE_MASK) {
+      any_mask = true;
+      if (y < m) {
+        const uint64_t* rw = a.row_bits + ((int64_t)o * m + y) * FAST_W;
+#pragma unroll
+        for (int q = 0; q < FAST_W; ++q) w[q] |= rw[q];
+      }
+    } else if (mode == MODE_BOX) {
+      const int r = sh.rad[o];
+      const int ya = max(0, sh.gy0[o] - r), yb = min(m - 1, sh.gy1[o] + r);
+      const int xa = max(0, sh.gx0[o] - r), xb = min(n - 1, sh.gx1[o] + r);
+      if (y < m && y >= ya && y <= yb) {
+#pragma unroll
+        for (int q = 0; q < FAST_W; ++q) {
+          const int lo = max(xa, 64 * q), hi = min(xb, 64 * q + 63);
+          if (lo <= hi) {
+            const int len = hi - lo + 1;
+            g[q] |= (len == 64 ? ~0ull : ((1ull << len) - 1ull)) << (lo - 64 * q);
+          }
+        }
+      }
+    }
+  }
+  if (!any_mask) return;   // the same for every thread
+  const int r = a.r_s;
+  row_dilate_regs(w, W, n, min(r, n));
+  if (y < m)
+#pragma unroll
+    for (int q = 0; q < FAST_W; ++q)
+      if (q < W) rows[y * W + q] = w[q];
+  lds_barrier();
   if (y < m) {
-    const uint8_t* rp = M + (int64_t)(y * s) * Wpx;
-    if (s == 1 && (n & 15) == 0 && (((uintptr_t)rp) & 15) == 0) {
-      for (int x0 = 0; x0 < n; x0 += 16) {
-        const u32x4 v = *(const u32x4*)(rp + x0);
-        uint32_t bits = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          uint32_t t = v[e];
-          t |= t >> 4;
-          t |= t >> 2;
-          t |= t >> 1;
-          bits |= ((t & 1u) | ((t >> 7) & 2u) | ((t >> 14) & 4u) | ((t >> 21) & 8u)) << (4 * e);
-        }
-        w[x0 >> 6] |= (uint64_t)bits << (x0 & 63);
-      }
-    } else {
-      for (int x = 0; x < n; ++x)
-        if (rp[x * s]) w[x >> 6] |= 1ull << (x & 63);
-    }
-  }
-  // bounding box in pixels.  s == 1: rows with a set cell (ballots) and the
-  // OR of all rows; otherwise a scan of every pixel.
-  if (s == 1) {
-    const uint64_t any = w[0] | w[1] | w[2] | w[3];
-    const unsigned long long rb = __ballot(any != 0ull);
-    if (lane == 0) sh.rowbits[wave] = rb;
-    // columns with a set cell: OR over the wave first, then one LDS atomic
-    // per wave and word (atomics of every lane on one address serialise)
-#pragma unroll
-    for (int q = 0; q < FAST_W; ++q) {
-      if (q >= W) break;
-      uint64_t c = w[q];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) c |= __shfl_xor(c, off, 64);
-      if (lane == 0 && c) atomicOr(&sh.colbits[q], (unsigned long long)c);
-    }
-  } else {
-    int y0 = 0x7fffffff, x0 = 0x7fffffff, y1 = -1, x1 = -1;
-    const int npx = Hpx * Wpx;
-    for (int p = tid; p < npx; p += SEL_THREADS)
-      if (M[p]) {
-        const int py = p / Wpx, px = p - py * Wpx;
-        y0 = min(y0, py);
-        y1 = max(y1, py);
-        x0 = min(x0, px);
-        x1 = max(x1, px);
-      }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      y0 = min(y0, __shfl_xor(y0, off, 64));
-      x0 = min(x0, __shfl_xor(x0, off, 64));
-      y1 = max(y1, __shfl_xor(y1, off, 64));
-      x1 = max(x1, __shfl_xor(x1, off, 64));
-    }
-    if (lane == 0 && y1 >= 0) {
-      atomicMin(&sh.bb[0], y0);
-      atomicMin(&sh.bb[1], x0);
-      atomicMax(&sh.bb[2], y1);
-      atomicMax(&sh.bb[3], x1);
-    }
-  }
-  lds_barrier();
-  if (tid == 0) {
-    int by0 = -1, bx0 = -1, by1 = -1, bx1 = -1;
-    if (s == 1) {
-      for (int q = 0; q < SEL_WAVES; ++q)
-        if (sh.rowbits[q]) {
-          const int lo = 64 * q + (int)__builtin_ctzll(sh.rowbits[q]);
-          const int hi = 64 * q + 63 - (int)__builtin_clzll(sh.rowbits[q]);
-          if (by0 < 0) by0 = lo;
-          by1 = hi;
-        }
-      for (int q = 0; q < W; ++q) {
-        const uint64_t c = sh.colbits[q];
-        sh.colbits[q] = 0ull;   // ready for the next object
-        if (c) {
-          if (bx0 < 0) bx0 = 64 * q + (int)__builtin_ctzll(c);
-          bx1 = 64 * q + 63 - (int)__builtin_clzll(c);
-        }
-      }
-    } else {
-      by0 = sh.bb[0];
-      bx0 = sh.bb[1];
-      by1 = sh.bb[2];
-      bx1 = sh.bb[3];
-      sh.bb[0] = 0x7fffffff;   // ready for the next object
-      sh.bb[1] = 0x7fffffff;
-      sh.bb[2] = -1;
-      sh.bb[3] = -1;
-    }
-    tracker_update(a, o, tw, by0, bx0, by1, bx1, sh);
-  }
-  lds_barrier();
-  const int mode = sh.mode, r = sh.r;
-  if (mode == MODE_BOX) {
-    const int ya = max(0, sh.gy0 - r), yb = min(m - 1, sh.gy1 + r);
-    const int xa = max(0, sh.gx0 - r), xb = min(n - 1, sh.gx1 + r);
-    if (y < m && y >= ya && y <= yb) {
-#pragma unroll
-      for (int q = 0; q < FAST_W; ++q) {
-        const int lo = max(xa, 64 * q), hi = min(xb, 64 * q + 63);
-        if (lo <= hi) {
-          const int len = hi - lo + 1;
-          g[q] |= (len == 64 ? ~0ull : ((1ull << len) - 1ull)) << (lo - 64 * q);
-        }
-      }
-    }
-  } else if (mode == MODE_MASK) {
-    row_dilate_regs(w, W, n, min(r, n));
-    if (y < m)
+    const int ya = max(0, y - r), yb = min(m - 1, y + r);
+    for (int yy = ya; yy <= yb; ++yy)
 #pragma unroll
       for (int q = 0; q < FAST_W; ++q)
-        if (q < W) rows[y * W + q] = w[q];
-    lds_barrier();
-    if (y < m) {
-      const int ya = max(0, y - r), yb = min(m - 1, y + r);
-      for (int yy = ya; yy <= yb; ++yy)
-#pragma unroll
-        for (int q = 0; q < FAST_W; ++q)
-          if (q < W) g[q] |= rows[yy * W + q];
-    }
+        if (q < W) g[q] |= rows[yy * W + q];
   }
-  // rows, rowbits and the mode words are rewritten by the next object
-  lds_barrier();
 }
 
 // One-wave prior for grids of at most 64 rows and stride 1 (wave 0 only, no
@@ -712,56 +687,18 @@ __device__ void add_object_prior_wave(const Rs3SelectArgs& a, int o, uint64_t* g
 }
 
 // Adds one object's prior into U (LDS byte map of the group).  bufA/bufB are
-// scratch areas of at least max(mn, 8*m*W) bytes.
+// scratch areas of at least max(mn, 8*m*W) bytes; sh holds the object's prior
+// words (objects_update).
 __device__ void add_object_prior(const Rs3SelectArgs& a, int o, uint8_t* U, uint8_t* bufA, uint8_t* bufB,
                                  SelShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m = a.m, n = a.n, s = a.s, mn = m * n;
   const int Wpx = n * s, Hpx = m * s;
   const uint8_t* M = a.masks + (int64_t)o * Hpx * Wpx;
-  if (tid == 0) {
-    sh.bb[0] = 0x7fffffff;
-    sh.bb[1] = 0x7fffffff;
-    sh.bb[2] = -1;
-    sh.bb[3] = -1;
-  }
-  __syncthreads();
-  // bounding box of the set pixels: per-thread, then per-wave, then 4 LDS atomics per wave
-  int y0 = 0x7fffffff, x0 = 0x7fffffff, y1 = -1, x1 = -1;
-  const int npx = Hpx * Wpx;
-  for (int p = tid; p < npx; p += SEL_THREADS) {
-    if (M[p]) {
-      const int y = p / Wpx, x = p - y * Wpx;
-      y0 = min(y0, y);
-      y1 = max(y1, y);
-      x0 = min(x0, x);
-      x1 = max(x1, x);
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    y0 = min(y0, __shfl_xor(y0, off, 64));
-    x0 = min(x0, __shfl_xor(x0, off, 64));
-    y1 = max(y1, __shfl_xor(y1, off, 64));
-    x1 = max(x1, __shfl_xor(x1, off, 64));
-  }
-  if (lane == 0 && y1 >= 0) {
-    atomicMin(&sh.bb[0], y0);
-    atomicMin(&sh.bb[1], x0);
-    atomicMax(&sh.bb[2], y1);
-    atomicMax(&sh.bb[3], x1);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int tw[RS3_TRACK_WORDS];
-    for (int w = 0; w < RS3_TRACK_WORDS; ++w) tw[w] = a.track[o * RS3_TRACK_WORDS + w];
-    tracker_update(a, o, tw, sh.bb[0], sh.bb[1], sh.bb[2], sh.bb[3], sh);
-  }
-  __syncthreads();
-  const int mode = sh.mode, r = sh.r;
+  const int mode = sh.mode[o], r = sh.rad[o];
   if (mode == MODE_BOX) {
-    const int ya = max(0, sh.gy0 - r), yb = min(m - 1, sh.gy1 + r);
-    const int xa = max(0, sh.gx0 - r), xb = min(n - 1, sh.gx1 + r);
+    const int ya = max(0, sh.gy0[o] - r), yb = min(m - 1, sh.gy1[o] + r);
+    const int xa = max(0, sh.gx0[o] - r), xb = min(n - 1, sh.gx1[o] + r);
     for (int i = tid; i < mn; i += SEL_THREADS) {
       const int y = i / n, x = i - y * n;
       if (y >= ya && y <= yb && x >= xa && x <= xb) U[i] = 1;
@@ -868,16 +805,15 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
   uint8_t* tmp = base + buf;
   uint8_t* rank_lds = tmp + buf;   // SEL_RANK_BYTES: candidate keys, cells, keep bits
 
-  // Contiguous cells per thread so that block scans follow cell order.  The
-  // energies and tracker words do not depend on the prior: load them first.
+  // The energies do not depend on the prior: load them first.
   const int cpt = (mn + SEL_THREADS - 1) / SEL_THREADS;
-  const int c0 = tid * cpt;
+  const int c0 = (tid >> 6) * 64 * cpt + lane;   // this thread's cells: c0 + 64 j, j < cpt
   const unsigned long long* ebits =
       reinterpret_cast<const unsigned long long*>(a.e + (a.x_per_obj ? (int64_t)g * mn : 0)) + c0;
   unsigned long long kreg[REG ? MAXC : 1];
   if (REG) {
 #pragma unroll
-    for (int j = 0; j < MAXC; ++j) kreg[REG ? j : 0] = (j < cpt && c0 + j < mn) ? ebits[j] : 0ull;
+    for (int j = 0; j < MAXC; ++j) kreg[REG ? j : 0] = (j < cpt && c0 + 64 * j < mn) ? ebits[64 * j] : 0ull;
   }
   // per-block energy ranges of this grid (wave 0, NR per lane), reduced later
   constexpr int NR = MAXC / 4 > 0 ? MAXC / 4 : 1;
@@ -892,13 +828,6 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
       rhi[q] = bk < n_eblk ? er[2 * bk + 1] : 0ull;
     }
   }
-  if (tid == 0) {
-    sh.bb[0] = 0x7fffffff;
-    sh.bb[1] = 0x7fffffff;
-    sh.bb[2] = -1;
-    sh.bb[3] = -1;
-  }
-  if (tid < 4) sh.colbits[tid] = 0ull;
   if (tid < 256) sh.hist[tid] = 0;
   const int W = (a.n + 63) >> 6;
   const bool fast = a.m <= SEL_THREADS && W <= FAST_W;
@@ -908,54 +837,39 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
     const uint64_t* pb = a.prior_bits + (int64_t)g * 64 * FAST_W;
     if (tid < a.m * W) Gs[tid] = pb[tid];
     lds_barrier();
-  } else if (fast && a.m <= 64 && a.s == 1) {
-    // one wave: lane y owns grid row y
-    if (tid < 64) {
+  } else {
+    const int o0 = a.union_objects ? 0 : g, no = a.union_objects ? a.n_obj : 1;
+    objects_update(a, o0, no, sh);
+    if (fast) {
+      uint64_t* rows = reinterpret_cast<uint64_t*>(tmp);
       uint64_t gw[FAST_W] = {0, 0, 0, 0};
-      if (a.union_objects) {
-        for (int o = 0; o < a.n_obj; ++o) add_object_prior_wave(a, o, gw);
-      } else {
-        add_object_prior_wave(a, g, gw);
-      }
+      lds_barrier();
+      add_priors_fast(a, o0, no, rows, gw, sh);
       if (tid < a.m)
 #pragma unroll
         for (int q = 0; q < FAST_W; ++q)
           if (q < W) Gs[tid * W + q] = gw[q];
-    }
-    lds_barrier();
-  } else if (fast) {
-    uint64_t* rows = reinterpret_cast<uint64_t*>(tmp);
-    uint64_t gw[FAST_W] = {0, 0, 0, 0};
-    lds_barrier();
-    if (a.union_objects) {
-      for (int o = 0; o < a.n_obj; ++o) add_object_prior_fast(a, o, rows, gw, sh);
+      lds_barrier();
     } else {
-      add_object_prior_fast(a, g, rows, gw, sh);
-    }
-    if (tid < a.m)
-#pragma unroll
-      for (int q = 0; q < FAST_W; ++q)
-        if (q < W) Gs[tid * W + q] = gw[q];
-    lds_barrier();
-  } else {
-    for (int i = tid; i < mn; i += SEL_THREADS) U[i] = 0;
-    __syncthreads();
-    if (a.union_objects) {
-      for (int o = 0; o < a.n_obj; ++o) add_object_prior(a, o, U, base, tmp, sh);
-    } else {
-      add_object_prior(a, g, U, base, tmp, sh);
+      for (int i = tid; i < mn; i += SEL_THREADS) U[i] = 0;
+      __syncthreads();
+      for (int o = o0; o < o0 + no; ++o) add_object_prior(a, o, U, base, tmp, sh);
     }
   }
-  // this thread's cells c0 .. c0+cpt-1 start at grid row cy, column cx
+  // this thread's first cell is grid row cy, column cx; each further cell is
+  // 64 cells on
   int cy = c0 / a.n, cx = c0 - cy * a.n;
+  const int dy = 64 / a.n, dx = 64 - dy * a.n;
   uint32_t inP = 0;
 #pragma unroll
   for (int j = 0; j < MAXC; ++j) {
-    if (j < cpt && c0 + j < mn) {
-      const bool in = fast ? ((Gs[cy * W + (cx >> 6)] >> (cx & 63)) & 1ull) : U[c0 + j] != 0;
+    if (j < cpt && c0 + 64 * j < mn) {
+      const bool in = fast ? ((Gs[cy * W + (cx >> 6)] >> (cx & 63)) & 1ull) : U[c0 + 64 * j] != 0;
       if (in) inP |= 1u << j;
-      if (++cx == a.n) {
-        cx = 0;
+      cx += dx;
+      cy += dy;
+      if (cx >= a.n) {
+        cx -= a.n;
         ++cy;
       }
     }
@@ -964,9 +878,9 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
     uint8_t* po = a.prior_out + (int64_t)g * mn + c0;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j)
-      if (j < cpt && c0 + j < mn) po[j] = (inP >> j) & 1u;
+      if (j < cpt && c0 + 64 * j < mn) po[64 * j] = (inP >> j) & 1u;
   }
-  auto key_of = [&](int j) -> unsigned long long { return REG ? kreg[REG ? j : 0] : ebits[j]; };
+  auto key_of = [&](int j) -> unsigned long long { return REG ? kreg[REG ? j : 0] : ebits[64 * j]; };
   const int k = a.k[g];
   int countP;
   block_scan_bits<MAXC>(inP, cpt, sh.red1, &countP);
@@ -1031,7 +945,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
             if (inB >> j & 1) {
               const int q = atomicAdd(&sh.ncand, 1);
               ck[q] = key_of(j);
-              ci[q] = c0 + j;
+              ci[q] = c0 + 64 * j;
             }
           lds_barrier();
           // exact rank of each boundary candidate among the candidates
@@ -1059,7 +973,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
               }
               rank += __popcll(__ballot(j < cntB && (kq > key || (kq == key && iq < idx))));
             }
-            if (lane == 0 && rank < rem) atomicOr(&kb[idx / cpt], 1u << (idx - (idx / cpt) * cpt));
+            if (lane == 0 && rank < rem) {
+              const int ow = idx / (64 * cpt), loc = idx - ow * 64 * cpt;   // the cell's owner: wave, offset
+              atomicOr(&kb[64 * ow + (loc & 63)], 1u << (loc >> 6));
+            }
           }
           lds_barrier();
           kp |= kb[tid];
@@ -1137,14 +1054,14 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
     keep = gt;
     if (!ge && k > 0) {
       int eqTot;
-      int eqBefore = block_excl_scan(__popc(eq), sh, &eqTot);
+      int eqBefore = block_scan_bits<MAXC>(eq, cpt, sh.red2, &eqTot);
 #pragma unroll
-      for (int j = 0; j < MAXC; ++j) {
-        if (eq >> j & 1) {
-          if (eqBefore < need_eq) keep |= 1u << j;
-          ++eqBefore;
+      for (int j = 0; j < MAXC; ++j)
+        if (j < cpt) {
+          const unsigned long long b = __ballot((eq >> j) & 1u);
+          if ((eq >> j & 1) && eqBefore + bits_below(b) < need_eq) keep |= 1u << j;
+          eqBefore += __popcll(b);
         }
-      }
     }
     }
   }
@@ -1153,15 +1070,19 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
   int32_t* out = a.sel_idx + (int64_t)g * mn;
 #pragma unroll
   for (int j = 0; j < MAXC; ++j)
-    if (keep >> j & 1) out[before++] = c0 + j;
+    if (j < cpt) {
+      const unsigned long long b = __ballot((keep >> j) & 1u);
+      if (keep >> j & 1) out[before + bits_below(b)] = c0 + 64 * j;
+      before += __popcll(b);
+    }
   if (tid == 0) a.sel_count[g] = total;
 }
 
-// The energies and, for grids of at most 64 rows and 256 columns at stride 1,
-// the one-wave prior of every group in one launch: the prior depends only on
-// the masks and the tracker state, the energies only on X, so the prior
-// blocks (after the energy blocks) run beside them and leave the group's
-// prior rows [m][W] in prior_bits for the selection.
+// The energies and, beside them (after the energy blocks), what the selection
+// needs of the masks, which depends on neither X nor the energies: for grids
+// of at most 64 rows and 256 columns at stride 1 the one-wave prior of every
+// group, whose rows [m][W] go to prior_bits; for the others the scan of every
+// mask row (row_scan), four rows per block.
 template <typename T, bool QP = false, bool WIDE = false>
 __global__ __launch_bounds__(256) void k_energy_prior(const T* __restrict__ X, int64_t x_stride, int mn, int C,
                                                       double* __restrict__ e, unsigned long long* __restrict__ range,
@@ -1171,7 +1092,7 @@ __global__ __launch_bounds__(256) void k_energy_prior(const T* __restrict__ X, i
   // the block-kind test would wait for the test's own load first
   asm volatile("" ::"s"(n_e), "s"(nbx), "s"(X), "s"(x_stride), "s"(mn), "s"(C), "s"(e), "s"(range),
                "s"(qp.WqT), "s"(qp.Qall), "s"(a.n), "s"(a.m), "s"(a.union_objects), "s"(a.n_obj), "s"(a.masks),
-               "s"(a.track), "s"(a.prior_bits));
+               "s"(a.track), "s"(a.prior_bits), "s"(a.row_box));
   const int b = blockIdx.x;
   if (b < n_e) {
     if constexpr (WIDE)
@@ -1181,6 +1102,12 @@ __global__ __launch_bounds__(256) void k_energy_prior(const T* __restrict__ X, i
     return;
   }
   const int g = b - n_e, tid = threadIdx.x;
+  if (a.row_box) {
+    const int q = 4 * g + (tid >> 6);
+    const int o = q / a.m;
+    if (o < a.n_obj) row_scan(a, o, q - o * a.m);
+    return;
+  }
   if (tid >= 64) return;
   const int W = (a.n + 63) >> 6;
   uint64_t gw[FAST_W] = {0, 0, 0, 0};
@@ -1211,33 +1138,6 @@ static bool energy_wide(int n_x, int mn, const Rs3QProjArgs* qp) {
   return !qp && (int64_t)n_x * ((mn + EW_ROWS - 1) / EW_ROWS) >= 256;
 }
 
-hipError_t rs3_launch_energy(const void* X, int64_t x_stride, int n_x, int mn, int C, int dtype,
-                             double* e, unsigned long long* range, hipStream_t st, const Rs3QProjArgs* qp) {
-  dim3 grid((mn + 63) / 64, n_x);
-  if (qp && !qproj_ok(C, dtype, qp)) return hipErrorInvalidValue;
-  if (energy_wide(n_x, mn, qp)) {
-    const dim3 gw((mn + EW_ROWS - 1) / EW_ROWS, n_x);
-    if (dtype == RS3_BF16)
-      RS3_LAUNCH(RS3_K_ENERGY, st, k_energy_wide<bf16_t>, gw, dim3(256), 0, st, (const bf16_t*)X, x_stride, mn, C, e,
-                 range);
-    else
-      RS3_LAUNCH(RS3_K_ENERGY, st, k_energy_wide<float>, gw, dim3(256), 0, st, (const float*)X, x_stride, mn, C, e,
-                 range);
-    return hipGetLastError();
-  }
-  const Rs3QProjArgs q = qp ? *qp : Rs3QProjArgs{};
-  if (qp)
-    RS3_LAUNCH(RS3_K_ENERGY, st, (k_energy<bf16_t, true>), grid, dim3(256), 0, st, (const bf16_t*)X, x_stride, mn, C,
-               e, range, q);
-  else if (dtype == RS3_BF16)
-    RS3_LAUNCH(RS3_K_ENERGY, st, k_energy<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)X, x_stride, mn, C, e,
-               range, q);
-  else
-    RS3_LAUNCH(RS3_K_ENERGY, st, k_energy<float>, grid, dim3(256), 0, st, (const float*)X, x_stride, mn, C, e,
-               range, q);
-  return hipGetLastError();
-}
-
 bool rs3_select_prior_beside(int m, int n, int s) { return m <= 64 && s == 1 && n <= 64 * FAST_W; }
 
 hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int mn, int C, int dtype, double* e,
@@ -1245,9 +1145,11 @@ hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int
                                    const Rs3QProjArgs* qp) {
   if (qp && !qproj_ok(C, dtype, qp)) return hipErrorInvalidValue;
   const Rs3QProjArgs q = qp ? *qp : Rs3QProjArgs{};
+  // blocks beside the energies: one per group, or one per four mask rows
+  const int n_more = a.row_box ? (a.n_obj * a.m + 3) / 4 : n_groups;
   if (energy_wide(n_x, mn, qp)) {
     const int nbw = (mn + EW_ROWS - 1) / EW_ROWS, n_w = nbw * n_x;
-    const dim3 gw(n_w + n_groups);
+    const dim3 gw(n_w + n_more);
     if (dtype == RS3_BF16)
       RS3_LAUNCH(RS3_K_ENERGY, st, (k_energy_prior<bf16_t, false, true>), gw, dim3(256), 0, st, (const bf16_t*)X,
                  x_stride, mn, C, e, range, a, nbw, n_w, q);
@@ -1257,7 +1159,7 @@ hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int
     return hipGetLastError();
   }
   const int nbx = (mn + 63) / 64, n_e = nbx * n_x;
-  const dim3 grid(n_e + n_groups);
+  const dim3 grid(n_e + n_more);
   if (qp)
     RS3_LAUNCH(RS3_K_ENERGY, st, (k_energy_prior<bf16_t, true>), grid, dim3(256), 0, st, (const bf16_t*)X, x_stride,
                mn, C, e, range, a, nbx, n_e, q);
