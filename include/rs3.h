@@ -225,13 +225,16 @@ rs3_status rs3_select_queries(const rs3_grid* g, int32_t n_obj, const uint8_t* m
  * sel_idx/sel_count : as produced by rs3_select_queries; sel_stride = m*n
  *          for per-object lists or 0 for one shared list
  * max_sel: upper bound on every sel_count used (host grid size), <= m*n
- * n_splits: key splits per query tile (0 = automatic); n_splits*H <= 256
+ * n_splits: key splits per query tile (0 = automatic); n_splits*H <= 256 (fp32
+ *          layers take at most 128/H of them)
  * Y      : [n_obj][m*n][C] with stride y_obj_stride (elements); may equal X
  *          (in place) only when n_obj == 1 or X is per object with the same
  *          stride.  y_fp32 = 1 writes Y as fp32 for diagnostics (never in
  *          place), otherwise Y has the layer dtype.
  * ws     : device workspace of at least rs3_readout_workspace_size() bytes (a
- *          size queried for max_sel also serves every smaller max_sel) */
+ *          size queried for max_sel also serves every smaller max_sel).
+ *          fp32 layers: optional; a call with less (or NULL) runs the direct
+ *          form, which uses none and is slower (results differ in rounding) */
 rs3_status rs3_readout_workspace_size(const rs3_layer* L, int32_t n_obj, int32_t max_sel,
                                       int32_t n_splits, size_t* bytes);
 rs3_status rs3_readout(const rs3_layer* L, const rs3_grid* g, int32_t n_obj,
@@ -256,7 +259,7 @@ rs3_status rs3_readout(const rs3_layer* L, const rs3_grid* g, int32_t n_obj,
  * for S key splits, Da the attention width (D, or d_kv in the absorbed form)
  * and H its heads.  E.g. one object on a 64x64 grid with one head of 256 fits
  * every max_sel up to 4096, with at most 6 key splits projected and 29
- * absorbed.  fp32 layers use no scratch.
+ * absorbed.  fp32 layers use no scratch (the direct form of rs3_readout).
  * Every call on one GPU shares that GPU's array, and no call clears it
  * (nothing in it must start at zero): calls that overlap in time on one GPU
  * (two streams, or two host threads) race and give undefined results. */

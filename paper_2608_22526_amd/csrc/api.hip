@@ -47,6 +47,7 @@ bool setup_done = false;
 rs3_status ensure_setup() {
   if (setup_done) return RS3_OK;
   hipError_t e = rs3_readout_setup();
+  if (e == hipSuccess) e = rs3_readout_f32_setup();
   if (e == hipSuccess) e = rs3_select_setup();
   if (e == hipSuccess) e = rs3_commit_setup();
   if (e == hipSuccess) e = rs3_fused_setup();
@@ -762,9 +763,31 @@ rs3_status rs3_attend(const void* Qh, const void* Kh, const void* Vh, int32_t n_
 static void readout_shape(const rs3_layer* L, int32_t n_obj, int32_t max_sel, int32_t S, size_t* q_bytes,
                           size_t* o_bytes, size_t* ml_bytes) {
   const LayerDev& ld = L->dev;
-  *q_bytes = align256((size_t)n_obj * max_sel * ld.Da * 2);
-  *o_bytes = align256((size_t)n_obj * S * max_sel * ld.Da * 2);
+  const size_t es = ld.dtype == RS3_F32 ? 4 : 2;
+  *q_bytes = align256((size_t)n_obj * max_sel * ld.Da * es);
+  *o_bytes = align256((size_t)n_obj * S * max_sel * ld.Da * es);
   *ml_bytes = align256((size_t)n_obj * S * max_sel * ld.Ha * 8);
+}
+
+// fp32 layers on the matrix cores: head widths the tiled kernels know.
+static bool f32_tiled_layer(const LayerDev& ld) {
+  return ld.dtype == RS3_F32 && (ld.dah == 32 || ld.dah == 64 || ld.dah == 128 || ld.dah == 256) && ld.C % 8 == 0;
+}
+
+// Key splits of an fp32 call: a work-group of 32 queries per CU, or two where
+// that leaves fewer than four splits, and no more than leave each wave one
+// half tile of the ring.  A frame of 256 queries, four heads of 64 and 4,096
+// keys takes 59.5 us with 8 splits (one work-group per CU), 63.5 with 16 and
+// 70.8 with 4; one of 192 queries, eight heads and three objects 70.5 with 3,
+// 78.1 with 2.  cap < 0: not bounded by the ring (workspace sizing).
+static int f32_splits(const LayerDev& ld, int32_t n_obj, int32_t max_sel, int32_t n_splits, int64_t cap) {
+  const int64_t wgs = (int64_t)n_obj * ld.Ha * ((max_sel + 31) / 32);
+  int64_t S = n_splits;
+  if (S == 0 && wgs > 0) S = 256 / wgs >= 4 ? 256 / wgs : 512 / wgs;
+  const int64_t most = n_splits > 0 || cap < 0 ? 64 : (cap + 127) / 128;
+  if (S > most) S = most;
+  if (S * ld.Ha > RS3_F32_MAX_SPLITS_X_HEADS) S = RS3_F32_MAX_SPLITS_X_HEADS / ld.Ha;
+  return S < 1 ? 1 : (int)S;
 }
 
 // kv_bytes < 0: the largest automatic choice (workspace sizing, where the
@@ -782,7 +805,16 @@ rs3_status rs3_readout_workspace_size(const rs3_layer* L, int32_t n_obj, int32_t
       n_splits * L->dev.Ha > RS3_MAX_SPLITS_X_HEADS)
     return RS3_E_INVALID;
   if (L->dev.dtype == RS3_F32) {
-    *bytes = 0;
+    // the largest layout over every max_sel' <= max_sel, as below
+    size_t best = 0;
+    if (f32_tiled_layer(L->dev))
+      for (int ms = 0; ms < max_sel;) {
+        ms = ms + 32 < max_sel ? ms + 32 : max_sel;
+        size_t q, o, ml;
+        readout_shape(L, n_obj, ms, f32_splits(L->dev, n_obj, ms, n_splits, -1), &q, &o, &ml);
+        if (q + o + ml > best) best = q + o + ml;
+      }
+    *bytes = best;
     return RS3_OK;
   }
   // The split count depends on max_sel, so take the largest layout over every
@@ -840,9 +872,15 @@ static rs3_status readout_args(const rs3_layer* L, const rs3_grid* g, int32_t n_
     const double kb = (double)banks[o]->host.cap * ld.dah * 4;
     if (kb > kv_bytes) kv_bytes = kb;
   }
-  int S = splits_for(L, n_obj, max_sel, n_splits, kv_bytes);
+  const bool f32 = ld.dtype == RS3_F32;
+  int64_t cap = 0;
+  for (int o = 0; o < n_obj; ++o) cap = std::max<int64_t>(cap, banks[o]->host.cap);
+  int S = f32 ? f32_splits(ld, n_obj, max_sel, n_splits, cap) : splits_for(L, n_obj, max_sel, n_splits, kv_bytes);
   size_t q, o_b, ml;
   readout_shape(L, n_obj, max_sel, S, &q, &o_b, &ml);
+  // fp32 calls without the workspace (or with other head widths) run the
+  // direct form, which needs none
+  if (f32 && (!f32_tiled_layer(ld) || !ws || !aligned16(ws) || ws_bytes < q + o_b + ml)) ws = nullptr;
   // fit_splits (automatic count into a fixed workspace): fewer key splits
   // until the partials fit
   while (fit_splits && n_splits == 0 && S > 1 && q + o_b + ml > ws_bytes) {
@@ -883,7 +921,7 @@ static rs3_status readout_args(const rs3_layer* L, const rs3_grid* g, int32_t n_
   a.n_obj = n_obj;
   a.max_sel = max_sel;
   a.S = S;
-  a.n_qt = (max_sel + 127) / 128;
+  a.n_qt = f32 ? (max_sel + 31) / 32 : (max_sel + 127) / 128;
   a.y_fp32 = y_fp32 ? 1 : 0;
   a.rope = ld.rope;
   a.stream_parts = 1;
@@ -1054,7 +1092,7 @@ rs3_status rs3_commit(rs3_bank* const* banks, int32_t n_obj, const rs3_grid* g, 
   st = ensure_setup();
   if (st != RS3_OK) return st;
   const LayerDev& ld = banks[0]->L->dev;
-  hipError_t e = rs3_launch_commit(a, ld.dtype, ld.d_kv, ld.Da, ld.Ha, ld.dah, (hipStream_t)stream);
+  hipError_t e = rs3_launch_commit(a, ld.dtype, ld.d_kv, ld.Da, (hipStream_t)stream);
   if (e != hipSuccess) return map_err(e);
   commit_done(banks, n_obj, pin);
   return RS3_OK;
@@ -1082,8 +1120,8 @@ rs3_status rs3_readout_commit(const rs3_layer* L, const rs3_grid* g, int32_t n_o
   bool pending = false;
   hipError_t e = rs3_launch_readout(ra, ab, ld.dtype, s, false, &pending);
   if (e == hipSuccess)
-    e = pending ? rs3_launch_merge_commit(ra, ca, ld.d_kv, s)
-                : rs3_launch_commit(ca, ld.dtype, ld.d_kv, ld.Da, ld.Ha, ld.dah, s);
+    e = pending ? rs3_launch_merge_commit(ra, ca, ld.dtype, ld.d_kv, s)
+                : rs3_launch_commit(ca, ld.dtype, ld.d_kv, ld.Da, s);
   if (e != hipSuccess) return map_err(e);
   commit_done(banks, n_obj, pin);
   return RS3_OK;
@@ -1166,8 +1204,8 @@ rs3_status rs3_frame(const rs3_layer* L, const rs3_grid* g, int32_t n_obj, rs3_t
   bool pending = false;
   if (e == hipSuccess) e = rs3_launch_readout(ra, ab, ld.dtype, s, false, &pending);
   if (e == hipSuccess)
-    e = pending ? rs3_launch_merge_commit(ra, ca, ld.d_kv, s)
-                : rs3_launch_commit(ca, ld.dtype, ld.d_kv, ld.Da, ld.Ha, ld.dah, s);
+    e = pending ? rs3_launch_merge_commit(ra, ca, ld.dtype, ld.d_kv, s)
+                : rs3_launch_commit(ca, ld.dtype, ld.d_kv, ld.Da, s);
   if (e != hipSuccess) return map_err(e);
   commit_done(banks, n_obj, io->pin);
   return RS3_OK;

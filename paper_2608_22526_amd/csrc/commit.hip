@@ -13,8 +13,8 @@
 //            than CUs): the raw K/V rows into the ring, their cells into
 //            `pos`, and their projections K^ = K W_k, V^ = V W_v into the
 //            tile-blocked attention layouts (bf16 MFMA with fp32
-//            accumulation, or fp32 FMA loops; the raw rows re-laid in
-//            absorbed mode).
+//            accumulation, or fp32 MFMA; the raw rows re-laid in absorbed
+//            mode).
 // k_commit_append_* / k_bank_tiles : the same append and tile rebuild for a
 //            bank restored from a snapshot (rows already in the ring).
 #include "commit_body.h"
@@ -61,7 +61,6 @@ __global__ __launch_bounds__(256) void k_commit_append_bf16(Rs3CommitArgs a) {
 // Restored bank: rows [hdr PSTART, + PLEN) of bank 0 from the raw ring,
 // 64 per work-group.
 __global__ __launch_bounds__(256) void k_commit_append_f32(Rs3CommitArgs a) {
-  __shared__ __attribute__((aligned(16))) float sK[64 * F32_SP], sV[64 * F32_SP], sW[64 * F32_WP];
   __shared__ int spos[64];
   const int o = blockIdx.x;
   const BankDev& b = *a.banks[o];
@@ -72,10 +71,10 @@ __global__ __launch_bounds__(256) void k_commit_append_f32(Rs3CommitArgs a) {
   const int rows = min(64, L - r0);
   if (threadIdx.x < 64) spos[threadIdx.x] = (int)threadIdx.x < rows ? b.pos[start + r0 + threadIdx.x] : 0;
   __syncthreads();
-  append_f32<256>(a, b, o, start, r0, rows, spos, sK, sV, sW);
+  append_f32<256>(a, b, o, start, r0, rows, spos, 0, 1);
 }
 
-// grid (n_obj, 1 + ceil(kept rows / rows_per_wg)), block CP_THREADS.
+// grid (n_obj, commit_blocks()), block CP_THREADS.
 template <bool BF16>
 __global__ __launch_bounds__(CP_THREADS) void k_commit(Rs3CommitArgs a) {
   extern __shared__ __attribute__((aligned(16))) int32_t dyn[];
@@ -99,15 +98,10 @@ hipError_t rs3_commit_setup() {
   return e;
 }
 
-hipError_t rs3_launch_commit(const Rs3CommitArgs& a, int dtype, int d_kv, int D, int H, int d_h,
-                             hipStream_t st) {
-  (void)D;
-  (void)H;
-  (void)d_h;
+hipError_t rs3_launch_commit(const Rs3CommitArgs& a, int dtype, int d_kv, int D, hipStream_t st) {
   const int mn = a.m * a.n;
   Rs3CommitArgs b = a;
-  b.rows_per_wg = commit_rows_per_wg(a.n_obj, mn);
-  const dim3 grid(a.n_obj, 1 + (mn + b.rows_per_wg - 1) / b.rows_per_wg);
+  const dim3 grid(a.n_obj, commit_blocks(b, dtype, D, mn));
   const size_t lds = CP_FMAX * 16 + commit_stage_bytes(dtype, d_kv);
   if (dtype == RS3_BF16)
     RS3_LAUNCH(RS3_K_COMMIT, st, k_commit<true>, grid, dim3(CP_THREADS), lds, st, b);

@@ -368,129 +368,114 @@ __device__ __forceinline__ void append_bf16(const Rs3CommitArgs& a, const BankDe
   }
 }
 
-// fp32: for d_kv <= 64 the kept rows are staged in LDS (sK, sV: 64 rows of
-// F32_STAGE_KV + 4 floats each), and so is each block of 64 rows of W_k^T or
-// W_v^T (sW: 64 x (d_kv + 1) floats, the odd pitch keeps the 64 lanes of a
-// wave, one output column each, on distinct banks); a thread computes the
-// output columns d0 + lane of the rows wave, wave + NT/64, ...  Otherwise
-// plain FMA loops over the rows just written to the ring.
-constexpr int F32_STAGE_KV = 64;
-constexpr int F32_SP = F32_STAGE_KV + 4;   // row pitch: 16-byte aligned rows
-constexpr int F32_WP = F32_STAGE_KV + 1;   // W block pitch
-
+// fp32: K^ = K W_k and V^ = V W_v on the fp32 matrix cores, one 32x32 output
+// block per wave and pass (two key halves x D/32 column blocks x {K, V}), the
+// operands straight from the source rows and the weights (L2): a block is
+// d_kv/2 MFMAs for d_kv/4 16-byte loads.  As in the bf16 form K^ is computed
+// keys x d and V^ transposed (d x keys), so that consecutive lanes store
+// consecutive words.  FMA loops over rows and weights staged in LDS, one
+// output per thread and step, took 69.8 us per commit of a dense 32x32 frame
+// at D = 256, d_kv = 64; this form 27.2 us with one work-group per 64 rows and
+// 13.4 us with `parts` of them, each with its share of the column blocks.
 template <int NT>
 __device__ __forceinline__ void append_f32(const Rs3CommitArgs& a, const BankDev& b, int o, int start, int r0,
-                                           int rows, const int* src, float* sK, float* sV, float* sW) {
-  const int tid = threadIdx.x;
+                                           int rows, const int* src, int part, int parts) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   const int d_kv = b.d_kv, d_h = b.d_h, H = b.H, D = H * d_h;
-  const bool stage = d_kv <= F32_STAGE_KV;
   const float* Km = (const float*)a.Kmem + (int64_t)o * a.kv_stride;
   const float* Vm = (const float*)a.Vmem + (int64_t)o * a.kv_stride;
   float* Kr = (float*)b.Kraw;
   float* Vr = (float*)b.Vraw;
-  for (int q = tid; q < rows * d_kv; q += NT) {
-    const int r = q / d_kv, c = q - r * d_kv;
-    const int64_t j = start + r0 + r;
-    float kv, vv;
-    if (a.from_ring) {
-      kv = gload(Kr + j * d_kv + c);
-      vv = gload(Vr + j * d_kv + c);
-    } else {
-      const int cell = src[r];
-      kv = gload(Km + (int64_t)cell * d_kv + c);
-      vv = gload(Vm + (int64_t)cell * d_kv + c);
-      gstore(Kr + j * d_kv + c, kv);
-      gstore(Vr + j * d_kv + c, vv);
-    }
-    if (stage) {
-      sK[r * F32_SP + c] = kv;
-      sV[r * F32_SP + c] = vv;
-    }
-  }
-  __syncthreads();   // also publishes the ring rows read back below
-  const float* WkT = (const float*)a.WkT;
-  const float* WvT = (const float*)a.WvT;
   float* Kh = (float*)b.Khat;
   float* Vh = (float*)b.Vhat;
-  if (stage) {
-    const int lane = tid & 63, wave = tid >> 6;
-    for (int pass = 0; pass < 2; ++pass) {
-      const float* WT = pass == 0 ? WkT : WvT;
-      const float* sX = pass == 0 ? sK : sV;
-      for (int d0 = 0; d0 < D; d0 += 64) {
-        const int nd = min(64, D - d0);
-        if (!a.absorb) {
-          for (int q = tid; q < nd * d_kv; q += NT) {
-            const int dd = q / d_kv, c = q - dd * d_kv;
-            sW[dd * F32_WP + c] = gload(WT + (int64_t)(d0 + dd) * d_kv + c);
-          }
-          __syncthreads();
-        }
-        const int d = d0 + lane;
-        if (lane < nd) {
-          const int h = d / d_h, dd = d - h * d_h;
-          for (int r = wave; r < rows; r += NT / 64) {
-            float acc;
-            if (a.absorb) {   // attention on the raw rows
-              acc = sX[r * F32_SP + d];
-            } else {
-              float a0 = 0.f, a1 = 0.f;
-              for (int c = 0; c < d_kv; c += 2) {   // d_kv is a multiple of 16
-                a0 = fmaf(sX[r * F32_SP + c], sW[lane * F32_WP + c], a0);
-                a1 = fmaf(sX[r * F32_SP + c + 1], sW[lane * F32_WP + c + 1], a1);
-              }
-              acc = a0 + a1;
-            }
-            const int j = start + r0 + r, tile = j >> 6, kk = j & 63;
-            if (pass == 0)
-              gstore(Kh + (((int64_t)tile * H + h) * KT + kk) * d_h + dd, acc);
-            else
-              gstore(Vh + (((int64_t)tile * H + h) * d_h + dd) * KT + vslot(kk), acc);
-          }
-        }
-        if (!a.absorb) __syncthreads();   // the next block rewrites sW
-      }
-    }
-  } else {
-    for (int q = tid; q < rows * D; q += NT) {
-      const int r = q / D, d = q - r * D;
+  auto krow = [&](int r) { return a.from_ring ? Kr + (int64_t)(start + r0 + r) * d_kv : Km + (int64_t)src[r] * d_kv; };
+  auto vrow = [&](int r) { return a.from_ring ? Vr + (int64_t)(start + r0 + r) * d_kv : Vm + (int64_t)src[r] * d_kv; };
+  const int cpr = d_kv / 4;
+  if (part == 0 && (!a.from_ring || a.absorb))
+    for (int q = tid; q < rows * cpr; q += NT) {
+      const int r = q / cpr, c = 4 * (q - r * cpr);
       const int j = start + r0 + r;
-      const float* kr = Kr + (int64_t)j * d_kv;
-      const float* vr = Vr + (int64_t)j * d_kv;
-      float sk, sv;
-      if (a.absorb) {  // attention on the raw rows
-        sk = gload(kr + d);
-        sv = gload(vr + d);
-      } else {
-        const float* wk = WkT + (int64_t)d * d_kv;
-        const float* wv = WvT + (int64_t)d * d_kv;
-        sk = 0.f;
-        sv = 0.f;
-        for (int c = 0; c < d_kv; ++c) {
-          sk = fmaf(gload(kr + c), gload(wk + c), sk);
-          sv = fmaf(gload(vr + c), gload(wv + c), sv);
+      const f32x4 kv = gload((const f32x4*)(krow(r) + c));
+      if (a.absorb) gstore((f32x4*)(Kh + ((int64_t)(j >> 6) * KT + (j & 63)) * d_kv + c), kv);
+      if (a.from_ring) continue;
+      gstore((f32x4*)(Kr + (int64_t)j * d_kv + c), kv);
+      gstore((f32x4*)(Vr + (int64_t)j * d_kv + c), gload((const f32x4*)(vrow(r) + c)));
+    }
+  if (a.absorb) {
+    // attention on the raw rows (one head of width d_kv): K^ rows above, V^
+    // rows transposed, consecutive lanes on consecutive keys of one row
+    for (int q = tid; q < rows * d_kv; q += NT) {
+      const int d = q / rows, r = q - d * rows;
+      const int j = start + r0 + r;
+      gstore(Vh + ((int64_t)(j >> 6) * d_kv + d) * KT + vslot(j & 63), gload(vrow(r) + d));
+    }
+    return;
+  }
+  const int lg_dh = (d_h & (d_h - 1)) == 0 ? 31 - __clz(d_h) : -1;
+  auto head_of = [&](int d) { return lg_dh >= 0 ? d >> lg_dh : d / d_h; };
+  const int nb_d = (D + 31) / 32, nu = d_kv / 8;   // units of 8 contraction channels (an even number)
+  // the 32x32 block of rows A (lane's row, 4g on) times columns B, four units
+  // of loads at a time (the 1,024-thread commit has 128 registers a thread),
+  // in two chains: shorter sums, and no wait on the step before
+  auto product = [&](const float* ar, const float* br) {
+    f32x16 c0 = {}, c1 = {};
+    for (int u0 = 0; u0 < nu; u0 += 4) {
+      f32x4 x[4], w[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int u = min(u0 + j, nu - 1);
+        x[j] = gload((const f32x4*)(ar + 8 * u));
+        w[j] = gload((const f32x4*)(br + 8 * u));
+      }
+#pragma unroll
+      for (int j = 0; j < 4; j += 2)
+        if (u0 + j < nu) {
+          c0 = mfma32f(x[j], w[j], c0);
+          c1 = mfma32f(x[j + 1], w[j + 1], c1);
+        }
+    }
+    return c0 + c1;
+  };
+  const int b0 = 4 * (part * nb_d / parts), b1 = 4 * ((part + 1) * nb_d / parts);
+  for (int blk = b0 + wave; blk < b1; blk += NT / 64) {
+    const int mb = blk & 1, is_v = (blk >> 1) & 1, nb = blk >> 2;
+    const int rr = 32 * mb + (lane & 31);   // key row fed by this lane
+    if (32 * mb >= rows) continue;
+    const int dcol = 32 * nb + (lane & 31);
+    const int rc = min(rr, rows - 1);
+    const int64_t wof = (int64_t)min(dcol, D - 1) * d_kv + 4 * g;
+    if (is_v) {   // rows = d, columns = keys
+      const f32x16 c = product((const float*)a.WvT + wof, vrow(rc) + 4 * g);
+      if (rr >= rows) continue;
+      const int j = start + r0 + rr;
+      const int64_t tb = (int64_t)(j >> 6) * H;
+      const int slot = vslot(j & 63);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int d = 32 * nb + c_row(r, lane);
+        if (d >= D) continue;
+        const int h = head_of(d);
+        gstore(Vh + ((tb + h) * d_h + (d - h * d_h)) * KT + slot, c[r]);
+      }
+    } else {      // rows = keys, columns = d
+      const f32x16 c = product(krow(rc) + 4 * g, (const float*)a.WkT + wof);
+      const int h = head_of(min(dcol, D - 1)), dd = dcol - h * d_h;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int kr = 32 * mb + c_row(r, lane);
+        float v = c[r];
+        if (a.rope) {
+          // Eq. 7 on the key side (lanes l and l^1 hold columns 2p and 2p+1)
+          const float w = __shfl_xor(v, 1);
+          const int cell = kr < rows ? min(max(src[kr], 0), a.rope_mn - 1) : 0;
+          const float* f = a.rope + (int64_t)cell * d_h + (min(dd, d_h - 1) & ~1);
+          v = v * gload(f) + ((dd & 1) ? w : -w) * gload(f + 1);
+        }
+        if (kr < rows && dcol < D) {
+          const int j = start + r0 + kr;
+          gstore(Kh + (((int64_t)(j >> 6) * H + h) * KT + (j & 63)) * d_h + dd, v);
         }
       }
-      const int tile = j >> 6, kk = j & 63, h = d / d_h, dd = d - h * d_h;
-      gstore(Kh + (((int64_t)tile * H + h) * KT + kk) * d_h + dd, sk);
-      gstore(Vh + (((int64_t)tile * H + h) * d_h + dd) * KT + vslot(kk), sv);
-    }
-  }
-  if (a.rope) {
-    // Eq. 7 on the key side: each K^ row written above turns by the factors
-    // of the cell it was kept from
-    __syncthreads();
-    const int hp = d_h / 2;
-    for (int q = tid; q < rows * (D / 2); q += NT) {
-      const int r = q / (D / 2), d = 2 * (q - r * (D / 2));
-      const int h = d / d_h, dd = d - h * d_h;
-      const int j = start + r0 + r, tile = j >> 6, kk = j & 63;
-      const int cell = min(max(src[r], 0), a.rope_mn - 1);
-      const float* f = a.rope + ((int64_t)cell * hp + (dd >> 1)) * 2;
-      float* kp = Kh + (((int64_t)tile * H + h) * KT + kk) * d_h + dd;
-      const float xe = kp[0], xo = kp[1];
-      kp[0] = xe * f[0] - xo * f[1];
-      kp[1] = xe * f[1] + xo * f[0];
     }
   }
 }
@@ -589,10 +574,12 @@ __device__ __forceinline__ void commit_block(const Rs3CommitArgs& a, int o, int 
     return;
   }
   if (!sh.ok) return;
-  // kept rows [(y-1)*rows_per_wg, y*rows_per_wg) of the new frame, 64 per round
+  // kept rows [rb*rows_per_wg, (rb+1)*rows_per_wg) of the new frame, 64 per
+  // round; the projections' column blocks are split over col_parts work-groups
   const int start = sh.start;
-  const int r_end = min(total, y * a.rows_per_wg);
-  for (int r0 = (y - 1) * a.rows_per_wg; r0 < r_end; r0 += 64) {
+  const int parts = BF16 ? 1 : a.col_parts, rb = (y - 1) / parts, part = (y - 1) - rb * parts;
+  const int r_end = min(total, (rb + 1) * a.rows_per_wg);
+  for (int r0 = rb * a.rows_per_wg; r0 < r_end; r0 += 64) {
     {   // kept cells of rows r0 .. r0+63
       int k = before;
       for (int j = 0; j < cpt; ++j)
@@ -603,12 +590,11 @@ __device__ __forceinline__ void commit_block(const Rs3CommitArgs& a, int o, int 
     }
     lds_barrier();
     const int rows = min(64, total - r0);
-    if (tid < rows) b.pos[start + r0 + tid] = spos[tid];
+    if (part == 0 && tid < rows) b.pos[start + r0 + tid] = spos[tid];
     if constexpr (BF16)
       append_bf16<CP_THREADS>(a, b, o, start, r0, rows, spos, (bf16_t*)stage);
     else
-      append_f32<CP_THREADS>(a, b, o, start, r0, rows, spos, (float*)stage, (float*)stage + 64 * F32_SP,
-                             (float*)stage + 2 * 64 * F32_SP);
+      append_f32<CP_THREADS>(a, b, o, start, r0, rows, spos, part, parts);
     __syncthreads();   // the next round rewrites spos and the row stage
   }
 }
@@ -623,8 +609,20 @@ inline int commit_rows_per_wg(int n_obj, int mn) {
   return 64 * (int)((blocks64 + CP_MAX_WGS - 1) / CP_MAX_WGS);
 }
 
+// Work-groups per object of a commit; sets the rows and, for projected fp32
+// layers, the column parts (64 columns each, while the call stays within two
+// work-groups per CU) that each of them takes.
+inline int commit_blocks(Rs3CommitArgs& a, int dtype, int D, int mn) {
+  a.rows_per_wg = commit_rows_per_wg(a.n_obj, mn);
+  const int nb = (mn + a.rows_per_wg - 1) / a.rows_per_wg;
+  a.col_parts = 1;
+  if (dtype == RS3_F32 && !a.absorb)
+    while (64 * (a.col_parts + 1) <= D && (int64_t)a.n_obj * nb * (a.col_parts + 1) <= 512) ++a.col_parts;
+  return 1 + nb * a.col_parts;
+}
+
 inline size_t commit_stage_bytes(int dtype, int d_kv) {
-  return dtype == RS3_BF16 ? (size_t)2 * 64 * (d_kv + 8) * 2 : (size_t)(2 * 64 * F32_SP + 64 * F32_WP) * 4;
+  return dtype == RS3_BF16 ? (size_t)2 * 64 * (d_kv + 8) * 2 : 0;   // fp32 rows are not staged
 }
 
 }  // namespace rs3

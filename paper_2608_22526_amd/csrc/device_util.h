@@ -89,6 +89,17 @@ __device__ __forceinline__ bool sel_ok(const int32_t* sel, int r, int mn) {
   return i >= 0 && i < mn && (r == 0 || sel[r - 1] < i);
 }
 
+// D = A(32x2) * B(2x32) + C.  Lane l supplies A row l%32 and B column l%32 at
+// k = l/32; the 16 results lie as in mfma32 (column l%32, rows c_row).
+// A contraction of 8 consecutive channels takes four of these on a 16-byte
+// chunk per operand: lane group g = l/32 holds channels 4g .. 4g+3 of the
+// eight, and step e multiplies channels e and 4+e.
+__device__ __forceinline__ f32x16 mfma32f(const f32x4& a, const f32x4& b, f32x16 c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], c, 0, 0, 0);
+  return c;
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dppf(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));

@@ -12,6 +12,7 @@
 // end at once (a work-group barrier waits only for the waves still running).
 #include "combine.h"
 #include "commit_body.h"
+#include "readout_f32.h"
 
 namespace rs3 {
 
@@ -38,9 +39,27 @@ __global__ __launch_bounds__(CP_THREADS) void k_merge_commit(Rs3ReadoutArgs ra, 
   }
 }
 
+// The same for fp32 layers.
+static_assert(MF_THREADS == CP_THREADS, "merge and commit blocks of one size");
+__global__ __launch_bounds__(CP_THREADS) void k_merge_commit_f32(Rs3ReadoutArgs ra, Rs3CommitArgs ca, int n_cb) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
+  const int b = blockIdx.x;
+  if (b < n_cb) {
+    merge_f32_block(ra, b % ra.n_obj, b / ra.n_obj, (float*)dyn);
+  } else {
+    const int c = b - n_cb;
+    commit_block<false>(ca, c % ca.n_obj, c / ca.n_obj, (int32_t*)dyn);
+  }
+}
+
 }  // namespace rs3
 
 using namespace rs3;
+
+static size_t merge_commit_f32_lds(int D, int HS, int d_kv) {
+  const size_t cb = merge_f32_lds(D, HS), cp = CP_FMAX * 16 + commit_stage_bytes(RS3_F32, d_kv);
+  return cb > cp ? cb : cp;
+}
 
 static size_t merge_commit_lds(int D, int d_kv) {
   const size_t cb = combine_lds_bytes(D), cp = CP_FMAX * 16 + commit_stage_bytes(RS3_BF16, d_kv);
@@ -59,7 +78,8 @@ hipError_t rs3_fused_setup() {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return hipFuncSetAttribute((const void*)k_merge_commit_f32, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)merge_commit_f32_lds(1024, RS3_F32_MAX_SPLITS_X_HEADS, 256));
 }
 
 // Work-groups of the fused launch beyond which the merge and the commit run
@@ -69,15 +89,22 @@ hipError_t rs3_fused_setup() {
 // separate at 64 objects of 898 selected rows).
 constexpr int FUSE_MAX_WGS = 1024;
 
-hipError_t rs3_launch_merge_commit(const Rs3ReadoutArgs& ra, const Rs3CommitArgs& ca, int d_kv, hipStream_t st) {
-  const int rb = cb_rows_for(ra.D, ra.n_obj, ra.max_sel), n_cb = ra.n_obj * ((ra.max_sel + rb - 1) / rb);
+hipError_t rs3_launch_merge_commit(const Rs3ReadoutArgs& ra, const Rs3CommitArgs& ca, int dtype, int d_kv,
+                                   hipStream_t st) {
+  const bool f32 = dtype == RS3_F32;
+  const int rb = f32 ? RF_ROWS : cb_rows_for(ra.D, ra.n_obj, ra.max_sel);
+  const int n_cb = ra.n_obj * ((ra.max_sel + rb - 1) / rb);
   const int mn = ca.m * ca.n;
   Rs3CommitArgs c = ca;
-  c.rows_per_wg = commit_rows_per_wg(ca.n_obj, mn);
-  const int n_cp = ca.n_obj * (1 + (mn + c.rows_per_wg - 1) / c.rows_per_wg);
+  const int n_cp = ca.n_obj * commit_blocks(c, dtype, ra.D, mn);
   if (n_cb + n_cp > FUSE_MAX_WGS) {
-    hipError_t e = rs3_launch_combine(ra, st);
-    return e == hipSuccess ? rs3_launch_commit(ca, RS3_BF16, d_kv, 0, 0, 0, st) : e;
+    hipError_t e = f32 ? rs3_launch_merge_f32(ra, st) : rs3_launch_combine(ra, st);
+    return e == hipSuccess ? rs3_launch_commit(ca, dtype, d_kv, ra.D, st) : e;
+  }
+  if (f32) {
+    RS3_LAUNCH(RS3_K_MERGE_COMMIT, st, k_merge_commit_f32, dim3(n_cb + n_cp), dim3(CP_THREADS),
+               merge_commit_f32_lds(ra.D, ra.H * ra.S, d_kv), st, ra, c, n_cb);
+    return hipGetLastError();
   }
   const size_t lds = merge_commit_lds(ra.D, d_kv);
   const dim3 grid(n_cb + n_cp), blk(CP_THREADS);

@@ -136,6 +136,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 constexpr int MIN_TILES_PER_SPLIT = 2;
 // Key splits times heads per readout call (bounds the merge kernel's LDS).
 #define RS3_MAX_SPLITS_X_HEADS 256
+// The same for fp32 layers, whose merge keeps 32 rows of 1,024 channels in LDS.
+#define RS3_F32_MAX_SPLITS_X_HEADS 128
 __host__ __device__ __forceinline__ int split_tiles(int ntiles, int S) {
   int tps = (ntiles + S - 1) / S;
   return tps < MIN_TILES_PER_SPLIT ? MIN_TILES_PER_SPLIT : tps;
@@ -195,6 +197,7 @@ struct Rs3CommitArgs {
   int from_ring;          // append: rows are already in the raw ring (bank import)
   uint64_t parity;        // bit o: current copy of bank o's frame table and frame count
   int rows_per_wg;        // commit: kept rows appended per work-group (a multiple of 64)
+  int col_parts;          // fp32 commit: work-groups that share the projections of those rows
   const float* rope;      // [rope_mn][d_h/2][2] rotary table for the keys, or null
   int rope_mn;
 };
@@ -210,11 +213,11 @@ struct Rs3ReadoutArgs {
   int sel_stride;         // elements between objects' lists (0 = shared)
   const void* WqT;        // [D][C]
   const void* WoT;        // [C][D]
-  void* Q;                // [n_obj][max_sel][D] bf16 workspace
-  void* Opart;            // [n_obj][S][max_sel][D] bf16 workspace
+  void* Q;                // [n_obj][max_sel][D] workspace in the layer's dtype (fp32 layers: null = direct form)
+  void* Opart;            // [n_obj][S][max_sel][D] workspace in the layer's dtype
   float* ML;              // [n_obj][S][max_sel][H][2] workspace
   float qscale;           // log2(e) / sqrt(d_h)
-  int mn, C, H, d_h, D, n_obj, max_sel, S, n_qt, y_fp32;
+  int mn, C, H, d_h, D, n_obj, max_sel, S, n_qt, y_fp32;   // n_qt: query tiles (128 rows, fp32 layers 32)
   const float* rope;      // [mn][d_h/2][2] rotary table for the queries, or null
   const void* Qall;       // queries of every cell projected by the energy launch (rs3_frame), or null:
   int64_t qall_stride;    //   [n_x][mn][64] bf16, elements between objects' grids (0 = shared)
@@ -307,17 +310,23 @@ bool rs3_select_prior_beside(int m, int n, int s);
 hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int mn, int C, int dtype, double* e,
                                    unsigned long long* range, const Rs3SelectArgs& a, int n_groups, hipStream_t st,
                                    const Rs3QProjArgs* qp = nullptr);
-hipError_t rs3_launch_commit(const Rs3CommitArgs& a, int dtype, int d_kv, int D, int H, int d_h,
-                             hipStream_t st);
+hipError_t rs3_launch_commit(const Rs3CommitArgs& a, int dtype, int d_kv, int D, hipStream_t st);
 // merge = false leaves the split merge of the bf16 path to the caller (the
 // fused merge + commit launch); returns whether a merge is pending in *pending.
 hipError_t rs3_launch_readout(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, int dtype, hipStream_t st,
                               bool merge = true, bool* pending = nullptr);
-// The readout's split merge and a commit in one launch (bf16 layers).
-hipError_t rs3_launch_merge_commit(const Rs3ReadoutArgs& ra, const Rs3CommitArgs& ca, int d_kv, hipStream_t st);
+// The readout's split merge and a commit in one launch.
+hipError_t rs3_launch_merge_commit(const Rs3ReadoutArgs& ra, const Rs3CommitArgs& ca, int dtype, int d_kv,
+                                   hipStream_t st);
 // The readout's split merge, output projection and residual scatter alone.
 hipError_t rs3_launch_combine(const Rs3ReadoutArgs& a, hipStream_t st);
 hipError_t rs3_fused_setup();
+// fp32 readout (readout_f32.hip): projection and attention into the workspace
+// (a.Q, a.Opart, a.ML), the merge, and the direct form that needs none.
+hipError_t rs3_launch_attn_f32(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st);
+hipError_t rs3_launch_merge_f32(const Rs3ReadoutArgs& a, hipStream_t st);
+hipError_t rs3_launch_readout_f32_direct(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st);
+hipError_t rs3_readout_f32_setup();
 // Split-KV attention only; project: the queries are projected from X[sel]
 // inside the kernel (heads of width <= 64), else read from a.Q.
 hipError_t rs3_launch_attn(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st, bool project);
