@@ -14,12 +14,13 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "librs3.so")
-SOURCES = ["host_check.cpp", "select.hip", "commit.hip", "readout.hip", "readout_f32.hip", "attend.hip", "rope.hip", "keepset.hip", "post.hip", "fused.hip", "stack.hip", "api.hip", "profile.hip"]
+SOURCES = ["host_check.cpp", "select.hip", "commit.hip", "readout.hip", "attn_tile.hip", "readout_f32.hip", "attend.hip", "rope.hip", "keepset.hip", "post.hip", "fused.hip", "stack.hip", "api.hip", "profile.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # The attention kernel keeps its MFMA accumulators in arch VGPRs, so the
 # online-softmax rescale is plain VALU work instead of AGPR round trips.
 PER_FILE = {"readout.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "readout_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+            "attn_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
             "fused.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -4,19 +4,21 @@
 // bf16 path (three kernels, plus a grid copy when Y is not X):
 //   k_qproj    gather the selected rows of X and project them,
 //              Q~ = X[sel] W_q * log2(e)/sqrt(d_h)  (32x32x16 bf16 MFMA);
-//   k_attn     split-KV flash attention over the resident 64-key tiles of
-//              the object's bank.  Each wave owns 32 queries and computes
-//              the transposed logits S^T = K^ Q~^T, so the 32 logits of a
-//              query sit in one lane (plus its partner lane l^32): the
-//              online-softmax max and sum need one cross-lane exchange.  The
-//              probabilities go straight from the accumulator registers into
-//              the B operand of O^T += V^T P^T (the V^ tile is stored with
-//              keys in MFMA slot order), K^/V^ tiles are staged in LDS;
+//   k_attn_tile (attn_tile.hip), or for one-wave launches of narrow heads, which
+//              project their queries themselves, k_attn / k_attn_g2: split-KV
+//              flash attention over the resident 64-key tiles of the object's
+//              bank.  Each wave owns 32 queries and computes the transposed
+//              logits S^T = K^ Q~^T, so that a query's logits sit in one lane
+//              and its partner l^32.  The probabilities go straight from the
+//              accumulator registers into the B operand of O^T += V^T P^T
+//              (the V^ tile is stored with keys in MFMA slot order), K^/V^
+//              tiles are staged in LDS;
 //   k_combine  merges the key splits (log-sum-exp weights), multiplies by
 //              W_o (MFMA), adds the residual and scatters y into Y[sel].
 // The fp32 path is in readout_f32.hip.
 #include <algorithm>
 
+#include "attn_util.h"
 #include "combine.h"
 
 namespace rs3 {
@@ -128,12 +130,6 @@ __device__ __forceinline__ AttnDmaOffsets<DH> attn_dma_offsets(int wave, int lan
   return d;
 }
 
-// One direct-to-LDS load: 16 bytes per lane from g into the wave's 1 KB at
-// lds_wave (lane l lands at lds_wave + 16 l).
-__device__ __forceinline__ void dma16(const void* g, void* lds_wave) {
-  __builtin_amdgcn_global_load_lds(g, lds_wave, 16, 0, 0);
-}
-
 // Direct-to-LDS loads of half tile `half` of bank tile `tile`, head h, into
 // a stage.  `tile`, `half` and `wave` are wave-uniform (scalar registers).
 template <int DH>
@@ -146,45 +142,6 @@ __device__ __forceinline__ void attn_issue(const bf16_t* Kh, const bf16_t* Vh, i
   for (int j = 0; j < L::NK / 4; ++j) dma16(kg + off.k[j], stage + (4 * j + wave) * 1024);
 #pragma unroll
   for (int j = 0; j < L::NV / 4; ++j) dma16(vg + off.v[j], stage + L::KREG + (4 * j + wave) * 1024);
-}
-
-// Value of lane l^32 for every lane (v_permlane32_swap: both halves come back
-// in registers; op(r[0], r[1]) combines a lane with its partner).
-__device__ __forceinline__ float max_with_partner(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __builtin_elementwise_maximum(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_with_partner(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Workgroup barrier without a memory fence: the fence of __syncthreads()
-// would wait for every outstanding load, including the K/V prefetches.
-// LDS stages are published by the explicit vmcnt waits before it.
-__device__ __forceinline__ void stage_barrier() { asm volatile("s_barrier" ::: "memory"); }
-
-// s_waitcnt encoding: wait until at most n vector-memory ops are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-// Waits until at most `later` stages of PW loads each are still in flight
-// (`later` is wave-uniform and at most MAXL).
-template <int PW, int MAXL>
-__device__ __forceinline__ void wait_stages(int later) {
-  if constexpr (MAXL >= 6) if (later >= 6) { wait_vmcnt<6 * PW>(); return; }
-  if constexpr (MAXL >= 5) if (later == 5) { wait_vmcnt<5 * PW>(); return; }
-  if constexpr (MAXL >= 4) if (later == 4) { wait_vmcnt<4 * PW>(); return; }
-  if constexpr (MAXL >= 3) if (later == 3) { wait_vmcnt<3 * PW>(); return; }
-  if constexpr (MAXL >= 2) if (later == 2) { wait_vmcnt<2 * PW>(); return; }
-  if (later == 1) {
-    wait_vmcnt<PW>();
-    return;
-  }
-  wait_vmcnt<0>();
 }
 
 // Query projection inside the attention (heads of width DH <= 64, d_model
@@ -295,33 +252,6 @@ __device__ __forceinline__ void attn_project(uint8_t* lds, int tid, int wave, in
 
 constexpr float RESCALE_LOG2 = 8.0f;
 
-// S^T (32 keys x 32 queries) of one half tile: K rows from LDS (kp points at
-// this lane's row and lane-group chunk), Q~ columns from registers.  CH = 2:
-// two accumulation chains (even / odd 16-deep steps) keep the MFMA pipe busy
-// when one half tile is scored at a time; CH = 1 when two independent half
-// tiles are scored together (no VALU sum of the chains).
-template <int DH, int CH = 2>
-__device__ __forceinline__ f32x16 attn_scores(const uint8_t* kp, const u32x4* qreg) {
-  constexpr int NKS = DH / 16;
-  constexpr int KG = NKS < 8 ? NKS : 8;
-  f32x16 s0 = f32x16{}, s1 = f32x16{};
-#pragma unroll
-  for (int k0 = 0; k0 < NKS; k0 += KG) {
-    u32x4 ka[KG];
-#pragma unroll
-    for (int j = 0; j < KG; ++j) ka[j] = *(const u32x4*)(kp + (k0 + j) * 32);
-#pragma unroll
-    for (int j = 0; j < KG; ++j) {
-      if (CH == 2 && (j & 1))
-        s1 = mfma32(ka[j], qreg[k0 + j], s1);
-      else
-        s0 = mfma32(ka[j], qreg[k0 + j], s0);
-    }
-  }
-  if constexpr (CH == 2) return s0 + s1;
-  return s0;
-}
-
 // Logits of two half tiles: all K operand reads are issued before the
 // MFMAs, so that the chain waits for LDS once rather than once per step.
 template <int DH>
@@ -344,40 +274,19 @@ __device__ __forceinline__ void attn_scores_pair(const uint8_t* ka, const uint8_
   }
 }
 
-// Maximum that propagates NaN (the logits hold none): v_maximum3_f32 needs
-// no canonicalising of its inputs, unlike fmaxf.
-__device__ __forceinline__ float max3f(float a, float b, float c) {
-  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
-}
-
-// Sum of the two bf16 values of a packed pair added to acc (v_dot2 with 1,1):
-// the row sums then add exactly the rounded probabilities the PV product uses.
-__device__ __forceinline__ float add_bf16x2(uint32_t p, float acc) {
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  const bf16x2_t one = {(__bf16)1.0f, (__bf16)1.0f};
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), one, acc, false);
-}
-
-// grid 8*n_qt*ceil(G/8) with G = n_obj*H*S key groups, block 256 (4 waves x
-// 32 queries).  Block b -> key group 8*((b>>3)/n_qt) + (b&7), query tile
-// (b>>3) % n_qt, so all query tiles of one key group share an XCD (and its L2).
-// PROJ: the queries are projected here from X[sel] and W_q (heads of width
-// <= 64); otherwise they are read from the projected buffer Q.
-// DEEP (launches of at most one work-group per CU, heads of width <= 64):
-// 8 stages and a loop over pairs of half tiles (two independent chains per
-// iteration for the one wave per SIMD); otherwise 4 stages and a loop over
-// single half tiles, which keeps the registers of several work-groups per CU.
-// NG = 2 (deep form with the projection only): eight waves, two groups of
-// four on the same 128 queries, each group taking every other pair of half
-// tiles, so that two waves share each SIMD; their partials are merged at the
-// end through LDS.
-template <int DH, bool PROJ, bool DEEP, int NG = 1>
-__global__ __launch_bounds__(256 * NG) void k_attn(Rs3ReadoutArgs a, int G) {
-  static_assert(NG == 1 || (NG == 2 && DEEP && PROJ), "two wave groups need the deep form");
-  constexpr int NT = 256 * NG;
+// The attention of launches whose heads are 32 wide at d_model 256 and that
+// fit the chip once: the queries are projected here from X[sel] and W_q.
+// grid 8*n_qt*ceil(G/8) with G = n_obj*H*S key groups, block 512: eight waves,
+// two groups of four on the same 128 queries, each group taking every other
+// pair of half tiles, so that two waves share each SIMD; their partials are
+// merged at the end through LDS.  Block b -> key group 8*((b>>3)/n_qt) + (b&7),
+// query tile (b>>3) % n_qt, so all query tiles of one key group share an XCD
+// (and its L2).
+template <int DH>
+__global__ __launch_bounds__(512) void k_attn(Rs3ReadoutArgs a, int G) {
+  constexpr int NG = 2, NT = 512;
   using L = AttnLds<DH>;
-  constexpr int nst = DEEP ? 8 : 4;   // LDS stages
-  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];   // nst * L::STAGE bytes
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];   // 8 stages
   const int bid = blockIdx.x;
   const int rest = bid >> 3;
   const int qt = rest % a.n_qt;
@@ -387,26 +296,19 @@ __global__ __launch_bounds__(256 * NG) void k_attn(Rs3ReadoutArgs a, int G) {
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5;
   const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave = wave_all & 3;                 // the wave's 32 queries: rows 32*wave of the tile
-  const int grp = NG == 2 ? wave_all >> 2 : 0;   // its group of key pairs
+  const int grp = wave_all >> 2;                 // its group of key pairs
   const int row0 = qt * 128;
   const int qrow = row0 + 32 * wave + (lane & 31);
   // Loads that need nothing but the arguments are issued before the chain
   // descriptor -> header -> tile list: the query operands (rows past the
-  // selected count are clamped into the buffers and zeroed below), or for
-  // PROJ the W_q chunks and the gathered row indices.
-  const int qrow_c = min(qrow, a.max_sel - 1);
+  // selected count are clamped into the buffers and zeroed below): the W_q
+  // chunks and the gathered row indices, those first, since the X loads wait
+  // for them alone.
   u32x4 qreg[DH / 16];
-  int src[PROJ ? PJ_XCH / NG : 1];
-  u32x4 wv[PROJ ? AttnProj<DH>::WCH / NG : 1];
-  if constexpr (PROJ) {
-    // the row indices first: the X loads wait for them alone
-    attn_proj_rows<NT>(a.sel_idx + (int64_t)o * a.sel_stride, row0, a.max_sel, tid, src);
-    attn_proj_load_w<DH, NT>((const bf16_t*)a.WqT, h, tid, wv);
-  } else {
-    const bf16_t* Qp = (const bf16_t*)a.Q + ((int64_t)o * a.max_sel + qrow_c) * a.D + h * DH;
-#pragma unroll
-    for (int ks = 0; ks < DH / 16; ++ks) qreg[ks] = gload((const u32x4*)(Qp + 16 * ks + 8 * g));
-  }
+  int src[PJ_XCH / NG];
+  u32x4 wv[AttnProj<DH>::WCH / NG];
+  attn_proj_rows<NT>(a.sel_idx + (int64_t)o * a.sel_stride, row0, a.max_sel, tid, src);
+  attn_proj_load_w<DH, NT>((const bf16_t*)a.WqT, h, tid, wv);
   // the bank descriptor's pointers (one cache line), by scalar loads
   const BankDev* bd = a.banks[o];
   const uint64_t p_hdr = sload((const uint64_t*)&bd->hdr);
@@ -420,15 +322,10 @@ __global__ __launch_bounds__(256 * NG) void k_attn(Rs3ReadoutArgs a, int G) {
     keep_s(p_tiles);
     keep_s(p_kh);
     keep_s(p_vh);
-    if constexpr (PROJ) {
 #pragma unroll
-      for (int i = 0; i < PJ_XCH / NG; ++i) keep(src[i]);
+    for (int i = 0; i < PJ_XCH / NG; ++i) keep(src[i]);
 #pragma unroll
-      for (int j = 0; j < AttnProj<DH>::WCH / NG; ++j) keep(wv[j]);
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < DH / 16; ++ks) keep(qreg[ks]);
-    }
+    for (int j = 0; j < AttnProj<DH>::WCH / NG; ++j) keep(wv[j]);
   };
   int cnt = sload(a.sel_count + (a.sel_stride ? o : 0));   // out of range: reported by the merge
   cnt = cnt < 0 ? 0 : min(cnt, a.max_sel);
@@ -437,21 +334,17 @@ __global__ __launch_bounds__(256 * NG) void k_attn(Rs3ReadoutArgs a, int G) {
     return;
   }
   const int32_t* hdr = (const int32_t*)p_hdr;
-  u32x4 xv[PROJ ? PJ_XCH / NG : 1];
-  if constexpr (PROJ) {
-    // the gathered X rows, in flight while the tile list arrives (invalid
-    // list entries read row 0; the merge kernel skips their rows)
-    attn_proj_load_x<NT>((const bf16_t*)a.X + (int64_t)o * a.x_stride, a.mn, tid, src, xv);
-  }
+  // the gathered X rows, in flight while the tile list arrives (invalid list
+  // entries read row 0; the merge kernel skips their rows)
+  u32x4 xv[PJ_XCH / NG];
+  attn_proj_load_x<NT>((const bf16_t*)a.X + (int64_t)o * a.x_stride, a.mn, tid, src, xv);
   const int ntiles = sload(hdr + HDR_NTILES);
   const int tps = split_tiles(ntiles, a.S);
   const int tb = min(s * tps, ntiles), te = min(tb + tps, ntiles);
   if (tb >= te) {
     keep_loads();
-    if constexpr (PROJ) {
 #pragma unroll
-      for (int i = 0; i < PJ_XCH / NG; ++i) keep(xv[i]);
-    }
+    for (int i = 0; i < PJ_XCH / NG; ++i) keep(xv[i]);
     // a split without tiles still holds a partial for each of its rows: the
     // empty one (m = -inf, l = 0), so that the merge reads every split
     if (g == 0 && grp == 0 && qrow < cnt) {
@@ -491,7 +384,7 @@ __global__ __launch_bounds__(256 * NG) void k_attn(Rs3ReadoutArgs a, int G) {
   }
   settle(c_tile, c_mlo, c_mhi);
   const bool qv = qrow < cnt;
-  if constexpr (PROJ) attn_project<DH, NT>(lds, tid, wave, lane, a.qscale, wv, xv, qreg);
+  attn_project<DH, NT>(lds, tid, wave, lane, a.qscale, wv, xv, qreg);
   // i-th visited half tile
   auto half_at = [&](int i) { int v = i + rot; return ub + (v >= nh ? v - nh : v); };
 #pragma unroll
@@ -504,7 +397,7 @@ __global__ __launch_bounds__(256 * NG) void k_attn(Rs3ReadoutArgs a, int G) {
   float m_run = -INFINITY, l_run = 0.f;
   const int kbase = (lane & 31) * L::KP + 16 * g;             // + ks*32
   const int vbase = L::KREG + (lane & 31) * L::VP + 16 * g;   // + dt*32*VP + q*32
-  if constexpr (NG == 2) {
+  {
     // Group g takes the pairs p = g, g+2, ... (pair p = half tiles 2p, 2p+1
     // in stages 2(p&3), 2(p&3)+1), so each group has two stage pairs.
     // Iteration j: wait for this wave's DMA of its pair p = 2j+g (issued one
@@ -629,206 +522,6 @@ __global__ __launch_bounds__(256 * NG) void k_attn(Rs3ReadoutArgs a, int G) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[dt][r] = acc[dt][r] * s0 + xs[(2 + 16 * dt + r) * 64] * s1;
     m_run = mm;
-  } else if constexpr (DEEP) {
-    // the first nst-2 half tiles; each pair iteration prefetches two more
-#pragma unroll
-    for (int j = 0; j < nst - 2; ++j)
-      if (j < nh) {
-        const int v = half_at(j);
-        const int tl = __builtin_amdgcn_readlane(c_tile, (v >> 1) - cbase);
-        attn_issue<DH>(Kh, Vh, tl, v & 1, h, H, lds + j * L::STAGE, wave, doff);
-      }
-
-    // Pairs of visited half tiles (nh is even; pair i/2 sits in stages i, i+1
-    // mod nst).  Iteration i: wait until its pair landed; barrier (the
-    // previous pair's stages are free); prefetch half tiles i+nst-2, i+nst-1
-    // into them; the logits of both halves (independent MFMA chains), one
-    // softmax update over the 64 keys, then O^T += V^T P^T for both.
-    const int smask = nst - 1;
-    for (int i = 0; i < nh; i += 2) {
-      wait_stages<L::PER_WAVE, nst - 2>(min(i + nst - 2, nh) - (i + 2));
-      stage_barrier();
-      const int u0 = half_at(i), u1 = half_at(i + 1);
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-        if (i + nst - 2 + k < nh) {
-          const int v = half_at(i + nst - 2 + k);
-          if ((v >> 1) - cbase >= 64) {
-            // (unrotated splits longer than the window, whose pairs are whole
-            // tiles) slide it to the tile being computed
-            wait_vmcnt<0>();
-            cbase = u0 >> 1;
-            c_tile = 0;
-            if (cbase + lane < te) c_tile = gload(&tiles[cbase + lane].tile);
-            const uint64_t mm = cbase + lane < te ? gload(&tiles[cbase + lane].mask) : 0ull;
-            c_mlo = (uint32_t)mm;
-            c_mhi = (uint32_t)(mm >> 32);
-            settle(c_tile, c_mlo, c_mhi);
-          }
-          const int tl = __builtin_amdgcn_readlane(c_tile, (v >> 1) - cbase);
-          attn_issue<DH>(Kh, Vh, tl, v & 1, h, H, lds + ((i + nst - 2 + k) & smask) * L::STAGE, wave, doff);
-        }
-      const uint8_t* SA = lds + (i & smask) * L::STAGE;
-      const uint8_t* SB = lds + ((i + 1) & smask) * L::STAGE;
-      const int t0 = (u0 >> 1) - cbase, t1 = (u1 >> 1) - cbase;
-      const uint32_t mA = (u0 & 1) ? __builtin_amdgcn_readlane(c_mhi, t0) : __builtin_amdgcn_readlane(c_mlo, t0);
-      const uint32_t mB = (u1 & 1) ? __builtin_amdgcn_readlane(c_mhi, t1) : __builtin_amdgcn_readlane(c_mlo, t1);
-      if ((mA | mB) == 0u) continue;
-      f32x16 sA = attn_scores<DH, 1>(SA + kbase, qreg);
-      f32x16 sB = attn_scores<DH, 1>(SB + kbase, qreg);
-      if (mA != 0xffffffffu) {   // partial or empty half tile (frame boundary)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (!(mA >> c_row(r, lane) & 1u)) sA[r] = -INFINITY;
-      }
-      if (mB != 0xffffffffu) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (!(mB >> c_row(r, lane) & 1u)) sB[r] = -INFINITY;
-      }
-      float mx = __builtin_elementwise_maximum(sA[0], sB[0]);
-#pragma unroll
-      for (int r = 1; r < 16; ++r) mx = max3f(mx, sA[r], sB[r]);
-      mx = max_with_partner(mx);
-      // Lazy rescale: the reference max only moves when a pair exceeds it by
-      // more than RESCALE_LOG2 (probabilities stay <= 2^RESCALE_LOG2); the
-      // accumulators are touched only when some lane of the wave moves.
-      const bool need = mx > m_run + RESCALE_LOG2;
-      if (__any(need)) {
-        const float m_new = need ? mx : m_run;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first pair
-        l_run *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DH / 32; ++dt) acc[dt] *= alpha;
-        m_run = m_new;
-      }
-      float psum = 0.f;
-      u32x4 pkA[2], pkB[2];
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float a0 = __builtin_amdgcn_exp2f(sA[8 * hf + 2 * j] - m_run);
-          const float a1 = __builtin_amdgcn_exp2f(sA[8 * hf + 2 * j + 1] - m_run);
-          const float b0 = __builtin_amdgcn_exp2f(sB[8 * hf + 2 * j] - m_run);
-          const float b1 = __builtin_amdgcn_exp2f(sB[8 * hf + 2 * j + 1] - m_run);
-          pkA[hf][j] = pack_bf16x2(a0, a1);
-          pkB[hf][j] = pack_bf16x2(b0, b1);
-          psum = add_bf16x2(pkB[hf][j], add_bf16x2(pkA[hf][j], psum));
-        }
-      l_run += psum;
-      // O^T += V^T P^T over the 64 keys (two 16-key MFMA steps per half and d block)
-#pragma unroll
-      for (int dt = 0; dt < DH / 32; ++dt) {
-        u32x4 va[4];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          va[q] = *(const u32x4*)(SA + vbase + dt * 32 * L::VP + q * 32);
-          va[2 + q] = *(const u32x4*)(SB + vbase + dt * 32 * L::VP + q * 32);
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[dt] = mfma32(va[q], pkA[q], acc[dt]);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) acc[dt] = mfma32(va[2 + q], pkB[q], acc[dt]);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < nst - 1; ++j)
-      if (j < nh) {
-        const int v = half_at(j);
-        const int tl = __builtin_amdgcn_readlane(c_tile, (v >> 1) - cbase);
-        attn_issue<DH>(Kh, Vh, tl, v & 1, h, H, lds + j * L::STAGE, wave, doff);
-      }
-
-    // stage 0 must land before its scores: later stages issued = min(nst-2, nh-1)
-    wait_stages<L::PER_WAVE, nst - 2>(min(nst - 2, nh - 1));
-    stage_barrier();
-
-    // Software pipeline over the visited half tiles i = 0 .. nh-1 (stage i%NST):
-    //   iteration i: wait until stage i+1 landed; barrier (stage i-1 free);
-    //   prefetch i+nst-1 into it; S^T(i+1) on the MFMA pipe while the VALU
-    //   does the softmax of i; then O^T += V^T(i) P(i).
-    const int smask = nst - 1;
-    f32x16 sc = attn_scores<DH>(lds + kbase, qreg);
-    for (int i = 0; i < nh; ++i) {
-      const int st = i & smask;
-      const int u = half_at(i);
-      if (i + 1 < nh) wait_stages<L::PER_WAVE, nst - 2>(min(i + nst - 2, nh - 1) - (i + 1));
-      stage_barrier();
-      if (i + nst - 1 < nh) {
-        const int v = half_at(i + nst - 1);
-        if ((v >> 1) - cbase >= 64) {
-          // (unrotated splits longer than the window) slide it to the tile
-          // being computed
-          wait_vmcnt<0>();
-          cbase = u >> 1;
-          c_tile = 0;
-          if (cbase + lane < te) c_tile = gload(&tiles[cbase + lane].tile);
-          const uint64_t mm = cbase + lane < te ? gload(&tiles[cbase + lane].mask) : 0ull;
-          c_mlo = (uint32_t)mm;
-          c_mhi = (uint32_t)(mm >> 32);
-          settle(c_tile, c_mlo, c_mhi);
-        }
-        const int tl = __builtin_amdgcn_readlane(c_tile, (v >> 1) - cbase);
-        attn_issue<DH>(Kh, Vh, tl, v & 1, h, H, lds + ((st + nst - 1) & smask) * L::STAGE, wave, doff);
-      }
-      const uint8_t* Sb = lds + st * L::STAGE;
-      const int tu = (u >> 1) - cbase;
-      const uint32_t msk = (u & 1) ? __builtin_amdgcn_readlane(c_mhi, tu) : __builtin_amdgcn_readlane(c_mlo, tu);
-
-      // S^T of the next half tile (independent of the softmax below).  In the
-      // last iteration the stage holds an earlier tile and the result is unused.
-      const f32x16 sc_next = attn_scores<DH>(lds + ((st + 1) & smask) * L::STAGE + kbase, qreg);
-
-      if (msk != 0u) {
-        if (msk != 0xffffffffu) {  // partial half tile (frame boundary)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (!(msk >> c_row(r, lane) & 1u)) sc[r] = -INFINITY;
-        }
-        float mx = __builtin_elementwise_maximum(sc[0], sc[1]);
-#pragma unroll
-        for (int r = 2; r < 16; r += 2) mx = max3f(mx, sc[r], sc[r + 1]);
-        mx = max_with_partner(mx);
-        // Lazy rescale: the reference max only moves when a half tile exceeds
-        // it by more than RESCALE_LOG2 (probabilities stay <= 2^RESCALE_LOG2);
-        // the accumulators are touched only when some lane of the wave moves.
-        const bool need = mx > m_run + RESCALE_LOG2;
-        if (__any(need)) {
-          const float m_new = need ? mx : m_run;
-          const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first tile
-          l_run *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < DH / 32; ++dt) acc[dt] *= alpha;
-          m_run = m_new;
-        }
-        float psum = 0.f;
-        u32x4 pk[2];
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float p0 = __builtin_amdgcn_exp2f(sc[8 * hf + 2 * j] - m_run);
-            const float p1 = __builtin_amdgcn_exp2f(sc[8 * hf + 2 * j + 1] - m_run);
-            pk[hf][j] = pack_bf16x2(p0, p1);
-            psum = add_bf16x2(pk[hf][j], psum);
-          }
-        l_run += psum;
-        // O^T += V^T P^T over the 32 keys (two 16-key MFMA steps per d block)
-        constexpr int DB = DH / 32 >= 2 ? 2 : 1;   // d blocks whose operands are fetched together
-#pragma unroll
-        for (int dt = 0; dt < DH / 32; dt += DB) {
-          u32x4 va[2 * DB];
-#pragma unroll
-          for (int q = 0; q < 2 * DB; ++q)
-            va[q] = *(const u32x4*)(Sb + vbase + (dt + (q >> 1)) * 32 * L::VP + (q & 1) * 32);
-#pragma unroll
-          for (int q = 0; q < 2 * DB; ++q) acc[dt + (q >> 1)] = mfma32(va[q], pk[q & 1], acc[dt + (q >> 1)]);
-        }
-      }
-      sc = sc_next;
-    }
   }
   const float l_tot = sum_with_partner(l_run);
   const float inv = l_tot > 0.f ? __builtin_amdgcn_rcpf(l_tot) : 0.f;
@@ -1393,17 +1086,10 @@ __global__ __launch_bounds__(256) void k_copy_grid16(const u32x4* X, int64_t x_s
 
 using namespace rs3;
 
-// Launches of at most one work-group per CU take the deep form of the
-// attention where its 8 stages fit the LDS (heads of width <= 64).
-constexpr int ATTN_DEEP_MAX_BLOCKS = 256;
-
-template <int DH, bool PROJ, bool DEEP, int NG = 1>
-static hipError_t launch_attn_dh(const Rs3ReadoutArgs& a, int G, int nblk, hipStream_t st) {
-  size_t lds = (size_t)(DEEP ? 8 : 4) * AttnLds<DH>::STAGE;
-  if constexpr (PROJ) lds = lds > (size_t)AttnProj<DH>::BYTES ? lds : (size_t)AttnProj<DH>::BYTES;
-  RS3_LAUNCH(RS3_K_ATTN, st, (k_attn<DH, PROJ, DEEP, NG>), dim3(nblk), dim3(256 * NG), lds, st, a, G);
-  return hipGetLastError();
-}
+// Launches of at most one work-group per CU with narrow heads project their
+// queries inside the attention.
+constexpr int ATTN_ONE_WAVE_BLOCKS = 256;
+constexpr int ATTN32_LDS = std::max(8 * AttnLds<32>::STAGE, AttnProj<32>::BYTES);
 
 // Launches of at most one work-group per CU with heads of width <= 64 at
 // d_model 256 project their queries inside the attention (the staged
@@ -1412,38 +1098,28 @@ static hipError_t launch_attn_dh(const Rs3ReadoutArgs& a, int G, int nblk, hipSt
 static bool attn_projects(const Rs3ReadoutArgs& a) {
   const int G = a.n_obj * a.H * a.S;
   const int nblk = 8 * a.n_qt * ((G + 7) / 8);
-  return a.d_h <= 64 && a.C == 8 * PJ_PC && nblk <= ATTN_DEEP_MAX_BLOCKS && !a.rope;
+  return a.d_h <= 64 && a.C == 8 * PJ_PC && nblk <= ATTN_ONE_WAVE_BLOCKS && !a.rope;
 }
 
 bool rs3_attn_projects(const Rs3ReadoutArgs& a) { return attn_projects(a); }
 
 hipError_t rs3_launch_attn(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st, bool project) {
+  if (!project) return rs3_launch_attn_tile(a, ab, st);
+  if (!attn_projects(a)) return hipErrorInvalidValue;
   const int G = a.n_obj * a.H * a.S;
   const int nblk = 8 * a.n_qt * ((G + 7) / 8);
-  if (project && !attn_projects(a)) return hipErrorInvalidValue;
-  const bool deep = nblk <= ATTN_DEEP_MAX_BLOCKS;
-  switch (a.d_h) {
-    case 32:
-      if (project) return launch_attn_dh<32, true, true, 2>(a, G, nblk, st);
-      return deep ? launch_attn_dh<32, false, true>(a, G, nblk, st) : launch_attn_dh<32, false, false>(a, G, nblk, st);
-    case 64:
-      if (project) {
-        const bool one = a.n_obj == 1;
-        if (a.Qall && one)
-          RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<true, true>), dim3(nblk), dim3(512), 8 * G2Lds::STAGE, st, a, G, ab);
-        else if (a.Qall)
-          RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<true, false>), dim3(nblk), dim3(512), 8 * G2Lds::STAGE, st, a, G, ab);
-        else if (one)
-          RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<false, true>), dim3(nblk), dim3(512), G2Lds::BYTES, st, a, G, ab);
-        else
-          RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<false, false>), dim3(nblk), dim3(512), G2Lds::BYTES, st, a, G, ab);
-        return hipGetLastError();
-      }
-      return deep ? launch_attn_dh<64, false, true>(a, G, nblk, st) : launch_attn_dh<64, false, false>(a, G, nblk, st);
-    case 128: return launch_attn_dh<128, false, false>(a, G, nblk, st);
-    case 256: return launch_attn_dh<256, false, false>(a, G, nblk, st);
-    default: return hipErrorInvalidValue;
-  }
+  const bool one = a.n_obj == 1;
+  if (a.d_h == 32)
+    RS3_LAUNCH(RS3_K_ATTN, st, k_attn<32>, dim3(nblk), dim3(512), ATTN32_LDS, st, a, G);
+  else if (a.Qall && one)
+    RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<true, true>), dim3(nblk), dim3(512), 8 * G2Lds::STAGE, st, a, G, ab);
+  else if (a.Qall)
+    RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<true, false>), dim3(nblk), dim3(512), 8 * G2Lds::STAGE, st, a, G, ab);
+  else if (one)
+    RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<false, true>), dim3(nblk), dim3(512), G2Lds::BYTES, st, a, G, ab);
+  else
+    RS3_LAUNCH(RS3_K_ATTN, st, (k_attn_g2<false, false>), dim3(nblk), dim3(512), G2Lds::BYTES, st, a, G, ab);
+  return hipGetLastError();
 }
 
 hipError_t rs3_launch_readout(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, int dtype, hipStream_t st, bool merge,
@@ -1517,21 +1193,14 @@ hipError_t rs3_readout_setup() {
   hipError_t e = hipFuncSetAttribute((const void*)k_combine<bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)max_lds);
   if (e != hipSuccess) return e;
-  // the attention's stages: 8 for heads of width <= 64, else 4
   const struct {
     const void* f;
     int bytes;
-  } attn[] = {{(const void*)k_attn<32, false, false>, 4 * AttnLds<32>::STAGE},
-              {(const void*)k_attn<32, false, true>, 8 * AttnLds<32>::STAGE},
-              {(const void*)k_attn<32, true, true, 2>, std::max(8 * AttnLds<32>::STAGE, AttnProj<32>::BYTES)},
-              {(const void*)k_attn<64, false, false>, 4 * AttnLds<64>::STAGE},
-              {(const void*)k_attn<64, false, true>, 8 * AttnLds<64>::STAGE},
+  } attn[] = {{(const void*)k_attn<32>, ATTN32_LDS},
               {(const void*)k_attn_g2<false, false>, G2Lds::BYTES},
               {(const void*)k_attn_g2<false, true>, G2Lds::BYTES},
               {(const void*)k_attn_g2<true, false>, 8 * G2Lds::STAGE},
-              {(const void*)k_attn_g2<true, true>, 8 * G2Lds::STAGE},
-              {(const void*)k_attn<128, false, false>, 4 * AttnLds<128>::STAGE},
-              {(const void*)k_attn<256, false, false>, 4 * AttnLds<256>::STAGE}};
+              {(const void*)k_attn_g2<true, true>, 8 * G2Lds::STAGE}};
   for (const auto& k : attn) {
     e = hipFuncSetAttribute(k.f, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
     if (e != hipSuccess) return e;

@@ -330,6 +330,9 @@ hipError_t rs3_readout_f32_setup();
 // Split-KV attention only; project: the queries are projected from X[sel]
 // inside the kernel (heads of width <= 64), else read from a.Q.
 hipError_t rs3_launch_attn(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st, bool project);
+// The form of launches with many work-groups (attn_tile.hip).
+hipError_t rs3_launch_attn_tile(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st);
+hipError_t rs3_attn_tile_setup();
 // Whether the attention of this launch projects its queries inside (then a
 // frame may hand it the energy launch's projection of every cell instead).
 bool rs3_attn_projects(const Rs3ReadoutArgs& a);

@@ -1,0 +1,84 @@
+"""The attention of launches with many work-groups, through rs3_attend, against
+fp64: every head width, sizes at the edges of its tiles (32 queries, 64 keys, a
+window of 64 tiles per split), logits that outgrow the first tile's reference,
+and infinities."""
+import numpy as np
+import pytest
+
+from workloads import storage_to_f64, to_storage
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _attend(Q, K, V, n_splits=0):
+    """bf16 storage [rows][H][d_h] -> (O, fp64 reference), each [n_q][H][d_h]."""
+    import paper_2608_22526_amd as rs3
+    from paper_2608_22526_amd.session import to_device, to_host
+    n_q, H, d_h = Q.shape
+    n_kv = K.shape[0]
+    ws = torch.zeros(max(rs3.attend_workspace_size(n_q, n_kv, H, d_h, rs3.RS3_BF16, n_splits), 256),
+                     dtype=torch.uint8, device="cuda")
+    O = torch.full((n_q, H, d_h), 7.0, dtype=torch.float32, device="cuda")
+    rs3.attend(to_device(Q), to_device(K), to_device(V), n_q, n_kv, H, d_h, rs3.RS3_BF16, O, ws, n_splits)
+    torch.cuda.synchronize()
+    q, k, v = (storage_to_f64(a, "bf16") for a in (Q, K, V))
+    ref = np.empty((n_q, H, d_h))
+    with np.errstate(invalid="ignore", over="ignore"):
+        for h in range(H):
+            s = q[:, h] @ k[:, h].T / np.sqrt(d_h)
+            p = np.exp(s - s.max(axis=1, keepdims=True))
+            ref[:, h] = (p / p.sum(axis=1, keepdims=True)) @ v[:, h]
+    return to_host(O).astype(np.float64), ref
+
+
+def _rand(rng, *shape, scale=1.0):
+    return to_storage((scale * rng.standard_normal(shape)).astype(np.float32), "bf16")
+
+
+@pytest.mark.parametrize("d_h,H", [(32, 8), (64, 3), (128, 2), (256, 1)])
+@pytest.mark.parametrize("n_q,n_kv,n_splits", [(1, 1, 0), (33, 63, 0), (129, 65, 2), (300, 4200, 1), (257, 4097, 5)])
+def test_tile_edges(d_h, H, n_q, n_kv, n_splits):
+    rng = np.random.default_rng(d_h + n_q + n_kv)
+    got, ref = _attend(_rand(rng, n_q, H, d_h, scale=2.0), _rand(rng, n_kv, H, d_h), _rand(rng, n_kv, H, d_h), n_splits)
+    # the queries are rounded to bf16 once more after scaling (2^-9 of a logit
+    # whose deviation is 2, so under 2 % of a weight at 5 deviations), the
+    # weights and the partials once each; |V| stays below 5
+    assert np.abs(got - ref).max() <= 5e-2
+    assert np.linalg.norm(got - ref) <= 1e-2 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("d_h", [32, 64, 128, 256])
+@pytest.mark.parametrize("rise", [40.0, 100.0, 160.0, 3000.0])
+def test_logits_far_above_the_first_tile(d_h, rise):
+    """Keys whose logits climb by `rise` (base 2) over the split, with gaps that
+    leave one key all the weight: within the range of the weights kept against
+    the first tile's maximum, and past it, where the split is run again."""
+    rng = np.random.default_rng(int(rise) + d_h)
+    n_q, n_kv = 40, 64 * 5
+    K = np.zeros((n_kv, 1, d_h), np.float32)
+    K[::64, 0, 0] = np.arange(5) / 4.0           # one climbing key per tile
+    K[1::64, 0, 0] = -1.0
+    Q = np.zeros((n_q, 1, d_h), np.float32)
+    Q[:, 0, 0] = rise * np.sqrt(d_h) / 1.4426950408889634
+    Q[1, 0, 0] *= -1.0                           # falls instead: every tile's keys at -1 share the weight
+    V = _rand(rng, n_kv, 1, d_h)
+    for n_splits in (1, 2):
+        got, ref = _attend(to_storage(Q, "bf16"), to_storage(K, "bf16"), V, n_splits)
+        assert np.abs(got - ref).max() <= 2e-2 * max(1.0, np.abs(ref).max())
+
+
+def test_infinite_keys():
+    """A key with an infinite channel: queries whose logit with it is -inf leave
+    the key out; where it is +inf the weights are undefined, and so is the row
+    (which has no positive weight sum and comes back 0)."""
+    rng = np.random.default_rng(3)
+    n_q, n_kv, d_h = 70, 200, 64
+    K = rng.standard_normal((n_kv, 1, d_h)).astype(np.float32)
+    K[150] = 0.0
+    K[150, 0, 0] = np.inf
+    Q = np.abs(rng.standard_normal((n_q, 1, d_h))).astype(np.float32) + 0.1
+    Q[::2, 0, 0] *= -1.0
+    got, ref = _attend(to_storage(Q, "bf16"), to_storage(K, "bf16"), _rand(rng, n_kv, 1, d_h), 1)
+    assert np.isnan(ref[1::2]).all() and (got[1::2] == 0.0).all()
+    assert np.abs(got[::2] - ref[::2]).max() <= 5e-2
