@@ -159,7 +159,8 @@ rs3_status rs3_layer_set_rope_axial(rs3_layer* L, int32_t m, int32_t n, double t
  * overlaps [start, start+L); (5) store rows and record (start, L, t, pinned).
  * Zero-length frames are recorded.  The bank stores the raw K/V rows, the
  * kept cell index (`pos`) per row, and the rows projected by W_k / W_v of
- * the layer it was created for (which must outlive it).
+ * the layer it was created for (whose memory stays until its last bank is
+ * destroyed, also when rs3_layer_destroy comes first).
  * Requires 0 <= n_pin < f_max <= 256, 1 <= cap <= 2^26. */
 rs3_status rs3_bank_create(const rs3_layer* L, int32_t cap, int32_t f_max,
                            int32_t n_pin, rs3_bank** out);

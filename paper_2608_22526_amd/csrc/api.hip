@@ -21,6 +21,7 @@ struct rs3_track {
 struct rs3_layer {
   LayerDev dev;         // host copy holding device pointers
   mutable int n_banks;  // banks created from the layer and not yet destroyed
+  bool destroyed;       // destroyed by the caller while banks were alive: freed with the last of them
 };
 
 struct rs3_bank {
@@ -276,12 +277,22 @@ rs3_status rs3_layer_create(int32_t C, int32_t H, int32_t d_kv, rs3_dtype dt, in
   return RS3_OK;
 }
 
-void rs3_layer_destroy(rs3_layer* L) {
-  if (!L) return;
+// Frees a layer that no bank refers to.
+static void layer_free(const rs3_layer* L) {
   void* w[5] = {L->dev.WqT, L->dev.WkT, L->dev.WvT, L->dev.WoT, L->dev.rope};
   for (void* p : w)
     if (p) (void)hipFree(p);
   delete L;
+}
+
+void rs3_layer_destroy(rs3_layer* L) {
+  if (!L) return;
+  // A bank counts itself out of its layer when it is destroyed.  A garbage
+  // collector may finalise the layer first, so the layer then waits for it.
+  if (L->n_banks > 0)
+    L->destroyed = true;
+  else
+    layer_free(L);
 }
 
 // ---- rotary table ------------------------------------------------------------
@@ -414,7 +425,7 @@ rs3_status rs3_bank_create(const rs3_layer* L, int32_t cap, int32_t f_max, int32
 
 void rs3_bank_destroy(rs3_bank* b) {
   if (!b) return;
-  b->L->n_banks--;
+  if (--b->L->n_banks == 0 && b->L->destroyed) layer_free(b->L);
   BankDev& h = b->host;
   void* ptrs[] = {h.Kraw, h.Vraw, h.pos, h.Khat, h.Vhat, h.hdr, h.frames, h.tiles, b->d_desc};
   for (void* p : ptrs)

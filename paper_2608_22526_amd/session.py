@@ -92,9 +92,11 @@ class Session:
         self._p_kept = self.kept_count.data_ptr()
         self._sel_stride = 0 if union_objects else self.mn
         self._y_stride = self.mn * C if n_obj > 1 else 0
-        self._dev_index = torch.device(device).index or 0
+        # (no reference to self: a session outside reference cycles gives its
+        # banks back as soon as it is dropped, and before its layer)
+        dev = torch.device(device).index or 0
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        self._raw_stream = (lambda: raw(self._dev_index)) if raw is not None else \
+        self._raw_stream = (lambda: raw(dev)) if raw is not None else \
             (lambda: torch.cuda.current_stream().cuda_stream)
 
     def _handles(self):
