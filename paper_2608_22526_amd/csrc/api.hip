@@ -629,7 +629,8 @@ static rs3_status select_args(const rs3_grid* g, int32_t n_obj, const uint8_t* m
 
 // Energies (beside them the priors or the scan of the mask rows, and with qp
 // every row's projected query), then the selection.
-static hipError_t select_launch(SelectLaunch& sl, hipStream_t st, const Rs3QProjArgs* qp = nullptr) {
+static hipError_t select_launch(SelectLaunch& sl, hipStream_t st, const Rs3QProjArgs* qp = nullptr,
+                                const Rs3CopyArgs* copy = nullptr) {
   Rs3SelectArgs& a = sl.a;
   hipError_t he;
   if (rs3_select_prior_beside(a.m, a.n, a.s)) {
@@ -639,7 +640,7 @@ static hipError_t select_launch(SelectLaunch& sl, hipStream_t st, const Rs3QProj
     a.row_box = (int32_t*)(sl.pbits + (size_t)a.n_obj * a.m * 4);
   }
   he = rs3_launch_energy_prior(sl.X, sl.x_stride, sl.n_x, sl.mn, sl.C, sl.dtype, sl.e, sl.erange, a, sl.n_groups, st,
-                               qp);
+                               qp, copy);
   if (he != hipSuccess) return he;
   return rs3_launch_select(a, sl.n_groups, st);
 }
@@ -1212,7 +1213,10 @@ rs3_status rs3_frame(const rs3_layer* L, const rs3_grid* g, int32_t n_obj, rs3_t
     ra.Qall = qp.Qall;
     ra.qall_stride = io->x_obj_stride ? (int64_t)mn * 64 : 0;
   }
-  hipError_t e = select_launch(sl, s, pre ? &qp : nullptr);
+  // an out-of-place frame's copy of the grid rides in the energy launch
+  const Rs3CopyArgs copy = rs3_grid_copy(ra, ld.dtype);
+  ra.copied = copy.Y != nullptr;
+  hipError_t e = select_launch(sl, s, pre ? &qp : nullptr, copy.Y ? &copy : nullptr);
   bool pending = false;
   if (e == hipSuccess) e = rs3_launch_readout(ra, ab, ld.dtype, s, false, &pending);
   if (e == hipSuccess)

@@ -73,6 +73,28 @@ __device__ __forceinline__ void keep_s(const T& v) {
   asm volatile("" ::"s"(v));
 }
 
+// Work-group blk of `blocks` (256 threads) of a grid copy: four chunks per
+// thread and round, read once and written to every copy.
+__device__ __forceinline__ void copy_block(const Rs3CopyArgs& c, int blk, int blocks) {
+  const int64_t total = c.n_x * c.count;
+  for (int64_t i0 = (int64_t)blk * 1024 + threadIdx.x; i0 < total; i0 += (int64_t)blocks * 1024) {
+    u32x4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = i0 + 256 * k < total ? i0 + 256 * k : total - 1, xi = c.n_x == 1 ? 0 : i / c.count;
+      v[k] = gload((const u32x4*)c.X + xi * c.x_stride + (i - xi * c.count));
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = i0 + 256 * k;
+      if (i >= total) break;
+      const int64_t xi = c.n_x == 1 ? 0 : i / c.count;
+      u32x4* y = (u32x4*)c.Y + xi * c.y_stride + (i - xi * c.count);
+      for (int p = 0; p < c.copies; ++p) gstore(y + p * c.y_stride, v[k]);
+    }
+  }
+}
+
 __device__ __forceinline__ int sel_count_of(const Rs3ReadoutArgs& a, int o, BankDev& b,
                                             bool report) {
   int cnt = gload(a.sel_count + (a.sel_stride ? o : 0));

@@ -24,9 +24,17 @@
 namespace rs3 {
 
 // ---------------------------------------------------------------------------
-// grid (n_obj, ceil(max_sel/64), D/64), block 256: 64 rows x 64 columns.
-__global__ __launch_bounds__(256) void k_qproj(Rs3ReadoutArgs a) {
-  const int o = blockIdx.x, r0 = blockIdx.y * 64, c0 = blockIdx.z * 64;
+// grid n_q + cp.blocks, block 256: blocks below n_q project 64 rows x 64
+// columns each (object fastest, then rows, then columns); the others copy the
+// grid of an out-of-place readout (the projection fills a few CUs for one
+// memory round trip, and the scatter comes later).
+__global__ __launch_bounds__(256) void k_qproj(Rs3ReadoutArgs a, int n_q, Rs3CopyArgs cp) {
+  if ((int)blockIdx.x >= n_q) {
+    copy_block(cp, blockIdx.x - n_q, cp.blocks);
+    return;
+  }
+  const int nr = (a.max_sel + 63) / 64, q0 = blockIdx.x / a.n_obj;
+  const int o = blockIdx.x % a.n_obj, r0 = (q0 % nr) * 64, c0 = (q0 / nr) * 64;
   BankDev& b = *a.banks[o];
   const int cnt = sel_count_of(a, o, b, false);   // reported by the merge kernel
   if (r0 >= cnt) return;
@@ -1072,15 +1080,8 @@ __global__ __launch_bounds__(256) void k_copy_grid(const InT* X, int64_t x_strid
   }
 }
 
-// 16-byte vector copy for same-type grids (count16 = bytes / 16 per object).
-__global__ __launch_bounds__(256) void k_copy_grid16(const u32x4* X, int64_t x_stride16, u32x4* Y,
-                                                     int64_t y_stride16, int64_t count16) {
-  const int o = blockIdx.y;
-  const u32x4* x = X + (int64_t)o * x_stride16;
-  u32x4* y = Y + (int64_t)o * y_stride16;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count16; i += (int64_t)gridDim.x * 256)
-    y[i] = x[i];
-}
+// The same for rows that keep their type.
+__global__ __launch_bounds__(256) void k_copy_grid16(Rs3CopyArgs c) { copy_block(c, blockIdx.x, c.blocks); }
 
 }  // namespace rs3
 
@@ -1122,27 +1123,39 @@ hipError_t rs3_launch_attn(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipS
   return hipGetLastError();
 }
 
+Rs3CopyArgs rs3_grid_copy(const Rs3ReadoutArgs& a, int dtype) {
+  Rs3CopyArgs c = {};
+  if (a.Y == a.X || (a.y_fp32 && dtype == RS3_BF16)) return c;
+  const int per = dtype == RS3_BF16 ? 8 : 4;   // elements per chunk
+  c.X = a.X;
+  c.Y = a.Y;
+  c.x_stride = a.x_stride / per;
+  c.y_stride = a.y_stride / per;
+  c.count = (int64_t)a.mn * a.C / per;
+  c.n_x = a.x_stride ? a.n_obj : 1;
+  c.copies = a.x_stride ? 1 : a.n_obj;
+  return c;
+}
+
 hipError_t rs3_launch_readout(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, int dtype, hipStream_t st, bool merge,
                               bool* pending) {
   if (pending) *pending = false;
-  const int64_t cells = (int64_t)a.mn * a.C;
-  const bool in_place = a.Y == a.X && !a.y_fp32;
-  if (!in_place) {
+  // the copy of an out-of-place readout: done by an earlier launch, beside the
+  // query projection, or in a launch of its own
+  const bool beside = a.max_sel > 0 && dtype == RS3_BF16 && !attn_projects(a);
+  Rs3CopyArgs cp = rs3_grid_copy(a, dtype);
+  if (a.copied) cp.Y = nullptr;
+  cp.blocks = cp.Y ? (int)std::min<int64_t>(2048, (cp.n_x * cp.count + 1023) / 1024) : 0;
+  if (cp.Y && !beside) {
+    RS3_LAUNCH(RS3_K_COPY, st, k_copy_grid16, dim3(cp.blocks), dim3(256), 0, st, cp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (a.y_fp32 && dtype == RS3_BF16) {   // a converting copy
+    const int64_t cells = (int64_t)a.mn * a.C;
     dim3 grid((unsigned)((cells + 255) / 256 < 2048 ? (cells + 255) / 256 : 2048), a.n_obj);
-    if (dtype == RS3_BF16 && !a.y_fp32) {
-      int64_t c16 = cells * 2 / 16;
-      dim3 g16((unsigned)((c16 + 255) / 256 < 2048 ? (c16 + 255) / 256 : 2048), a.n_obj);
-      RS3_LAUNCH(RS3_K_COPY, st, k_copy_grid16, g16, dim3(256), 0, st, (const u32x4*)a.X, a.x_stride * 2 / 16,
-                         (u32x4*)a.Y, a.y_stride * 2 / 16, c16);
-    } else if (dtype == RS3_BF16) {
-      RS3_LAUNCH(RS3_K_COPY, st, (k_copy_grid<bf16_t, float>), grid, dim3(256), 0, st, (const bf16_t*)a.X,
-                         a.x_stride, (float*)a.Y, a.y_stride, cells);
-    } else {
-      int64_t c16 = cells * 4 / 16;
-      dim3 g16((unsigned)((c16 + 255) / 256 < 2048 ? (c16 + 255) / 256 : 2048), a.n_obj);
-      RS3_LAUNCH(RS3_K_COPY, st, k_copy_grid16, g16, dim3(256), 0, st, (const u32x4*)a.X, a.x_stride * 4 / 16,
-                         (u32x4*)a.Y, a.y_stride * 4 / 16, c16);
-    }
+    RS3_LAUNCH(RS3_K_COPY, st, (k_copy_grid<bf16_t, float>), grid, dim3(256), 0, st, (const bf16_t*)a.X, a.x_stride,
+               (float*)a.Y, a.y_stride, cells);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1159,7 +1172,8 @@ hipError_t rs3_launch_readout(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, i
   }
   const bool project = attn_projects(a);
   if (!project) {
-    RS3_LAUNCH(RS3_K_QPROJ, st, k_qproj, dim3(a.n_obj, (a.max_sel + 63) / 64, a.D / 64), dim3(256), 0, st, a);
+    const int n_q = a.n_obj * ((a.max_sel + 63) / 64) * (a.D / 64);
+    RS3_LAUNCH(RS3_K_QPROJ, st, k_qproj, dim3(n_q + cp.blocks), dim3(256), 0, st, a, n_q, cp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

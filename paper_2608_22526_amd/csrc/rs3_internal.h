@@ -184,6 +184,18 @@ struct Rs3QProjArgs {
   float qscale;             // log2(e) / sqrt(d_h)
 };
 
+// The out-of-place readout's copy of the token grid, run inside a launch that
+// goes before the scatter: grid xi of n_x goes to `copies` output grids (n_x =
+// 1 and copies = n_obj for a grid shared by the objects, else n_obj and 1).
+// Counts and strides in 16-byte chunks.
+struct Rs3CopyArgs {
+  const void* X;
+  void* Y;                // null: nothing to copy
+  int64_t x_stride, y_stride, count;
+  int n_x, copies;
+  int blocks;             // work-groups added to the launch for it (0: its own loads carry the copy)
+};
+
 struct Rs3CommitArgs {
   rs3::BankDev* banks[RS3_MAX_OBJ];
   const uint8_t* masks;   // [n_obj][m*s][n*s]
@@ -221,6 +233,7 @@ struct Rs3ReadoutArgs {
   const float* rope;      // [mn][d_h/2][2] rotary table for the queries, or null
   const void* Qall;       // queries of every cell projected by the energy launch (rs3_frame), or null:
   int64_t qall_stride;    //   [n_x][mn][64] bf16, elements between objects' grids (0 = shared)
+  int copied;             // 1: an earlier launch has copied X to Y
   int stream_parts;       // 1: the split partials are stored non-temporally (the readout's merge
                           //   reads them once, non-temporally); 0: plain stores (stack, attend)
 };
@@ -306,10 +319,11 @@ hipError_t rs3_launch_select(const Rs3SelectArgs& a, int n_groups, hipStream_t s
 bool rs3_select_prior_beside(int m, int n, int s);
 // Energies and, in the same launch, the one-wave priors (a.prior_bits) or the
 // scan of the mask rows (a.row_box).  qp (optional, bf16 grids of 256
-// channels only): the launch also projects every row (Rs3QProjArgs).
+// channels only): the launch also projects every row (Rs3QProjArgs).  copy
+// (optional): it also copies the grid.
 hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int mn, int C, int dtype, double* e,
                                    unsigned long long* range, const Rs3SelectArgs& a, int n_groups, hipStream_t st,
-                                   const Rs3QProjArgs* qp = nullptr);
+                                   const Rs3QProjArgs* qp = nullptr, const Rs3CopyArgs* copy = nullptr);
 hipError_t rs3_launch_commit(const Rs3CommitArgs& a, int dtype, int d_kv, int D, hipStream_t st);
 // merge = false leaves the split merge of the bf16 path to the caller (the
 // fused merge + commit launch); returns whether a merge is pending in *pending.
@@ -333,6 +347,9 @@ hipError_t rs3_launch_attn(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipS
 // The form of launches with many work-groups (attn_tile.hip).
 hipError_t rs3_launch_attn_tile(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st);
 hipError_t rs3_attn_tile_setup();
+// The copy of an out-of-place readout whose rows keep their type (Y null when
+// the readout is in place or converts).
+Rs3CopyArgs rs3_grid_copy(const Rs3ReadoutArgs& a, int dtype);
 // Whether the attention of this launch projects its queries inside (then a
 // frame may hand it the energy launch's projection of every cell instead).
 bool rs3_attn_projects(const Rs3ReadoutArgs& a);

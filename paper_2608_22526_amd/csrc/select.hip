@@ -12,7 +12,9 @@
 //            MSB-first radix select over the fp64 bit patterns (energies are
 //            >= 0, so unsigned order is numeric order) and emits the kept
 //            cells in ascending order with two ordered block scans.
-#include "rs3_internal.h"
+#include <algorithm>
+
+#include "device_util.h"
 
 namespace rs3 {
 
@@ -66,7 +68,7 @@ constexpr int EB_CH = 32;
 template <typename T, bool QP = false>
 __device__ __forceinline__ void energy_block(const T* __restrict__ X, int64_t x_stride, int mn, int C,
                                              double* __restrict__ e, unsigned long long* __restrict__ range,
-                                             int bx, int xi, int nbx, const Rs3QProjArgs* qp = nullptr) {
+                                             int bx, int xi, int nbx, const Rs3QProjArgs* qp, u32x4* y) {
   __shared__ u32x4 rows[64 * (EB_CH + 1)];
   const int r0 = bx * 64, tid = threadIdx.x;
   const int nrows = min(64, mn - r0);
@@ -90,6 +92,13 @@ __device__ __forceinline__ void energy_block(const T* __restrict__ X, int64_t x_
       if (q < 64 * nch) {
         const int r = q / nch, c = q - r * nch;
         rows[r * (EB_CH + 1) + c] = v[k];
+      }
+    }
+    if (y) {   // the rows' copy in the output grid
+#pragma unroll
+      for (int k = 0; k < 64 * EB_CH / 256; ++k) {
+        const int q = tid + 256 * k, r = q / nch, c = q - r * nch;
+        if (r < nrows) gstore(y + (int64_t)(r0 + r) * cpr + cb + c, v[k]);
       }
     }
     __syncthreads();
@@ -167,7 +176,7 @@ constexpr int EW_ROWS = 256;
 template <typename T>
 __device__ __forceinline__ void energy_block_wide(const T* __restrict__ X, int64_t x_stride, int mn, int C,
                                                   double* __restrict__ e, unsigned long long* __restrict__ range,
-                                                  int bx, int xi) {
+                                                  int bx, int xi, u32x4* y) {
   __shared__ u32x4 rows[EW_ROWS * (EW_CH + 1)];
   const int r0 = bx * EW_ROWS, tid = threadIdx.x;
   const int nrows = min(EW_ROWS, mn - r0);
@@ -197,6 +206,7 @@ __device__ __forceinline__ void energy_block_wide(const T* __restrict__ X, int64
       const int q = tid + EW_ROWS * k;
       const int r = q / EW_CH, c = q % EW_CH;
       if (c < nch) rows[r * (EW_CH + 1) + c] = v[k];
+      if (y && c < nch && r < nrows) gstore(y + (int64_t)(r0 + r) * cpr + cb + c, v[k]);
     }
     __syncthreads();
     if (pass + 1 < npass) load(cb + EW_CH);
@@ -1082,23 +1092,35 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(Rs3SelectArgs a) {
 // needs of the masks, which depends on neither X nor the energies: for grids
 // of at most 64 rows and 256 columns at stride 1 the one-wave prior of every
 // group, whose rows [m][W] go to prior_bits; for the others the scan of every
-// mask row (row_scan), four rows per block.
+// mask row (row_scan), four rows per block.  An out-of-place frame's copy of
+// the grid rides along too: the energy blocks hold the rows in registers and
+// store them (64 objects with a grid each: 36 + 41 us as two launches, 54
+// as one; one object 6.4 + 2.7, now 7.1), or, where one grid goes to several
+// objects, blocks of their own write the copies, since 64 energy blocks would
+// store all of them alone (eight objects: 6.4 + 6.0 us, now 8.4).
 template <typename T, bool QP = false, bool WIDE = false>
 __global__ __launch_bounds__(256) void k_energy_prior(const T* __restrict__ X, int64_t x_stride, int mn, int C,
                                                       double* __restrict__ e, unsigned long long* __restrict__ range,
-                                                      Rs3SelectArgs a, int nbx, int n_e, Rs3QProjArgs qp) {
+                                                      Rs3SelectArgs a, int nbx, int n_e, int n_more,
+                                                      Rs3QProjArgs qp, Rs3CopyArgs cp) {
   // the arguments of both kinds of block in one batch of loads: the argument
   // block is memory the host wrote just before the launch, and loads behind
   // the block-kind test would wait for the test's own load first
   asm volatile("" ::"s"(n_e), "s"(nbx), "s"(X), "s"(x_stride), "s"(mn), "s"(C), "s"(e), "s"(range),
                "s"(qp.WqT), "s"(qp.Qall), "s"(a.n), "s"(a.m), "s"(a.union_objects), "s"(a.n_obj), "s"(a.masks),
-               "s"(a.track), "s"(a.prior_bits), "s"(a.row_box));
+               "s"(a.track), "s"(a.prior_bits), "s"(a.row_box), "s"(cp.Y), "s"(cp.blocks), "s"(cp.y_stride));
   const int b = blockIdx.x;
   if (b < n_e) {
+    const int xi = b / nbx;
+    u32x4* y = cp.Y && cp.blocks == 0 ? (u32x4*)cp.Y + xi * cp.y_stride : nullptr;
     if constexpr (WIDE)
-      energy_block_wide<T>(X, x_stride, mn, C, e, range, b % nbx, b / nbx);
+      energy_block_wide<T>(X, x_stride, mn, C, e, range, b - xi * nbx, xi, y);
     else
-      energy_block<T, QP>(X, x_stride, mn, C, e, range, b % nbx, b / nbx, nbx, &qp);
+      energy_block<T, QP>(X, x_stride, mn, C, e, range, b - xi * nbx, xi, nbx, &qp, y);
+    return;
+  }
+  if (b >= n_e + n_more) {
+    copy_block(cp, b - n_e - n_more, cp.blocks);
     return;
   }
   const int g = b - n_e, tid = threadIdx.x;
@@ -1142,33 +1164,35 @@ bool rs3_select_prior_beside(int m, int n, int s) { return m <= 64 && s == 1 && 
 
 hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int mn, int C, int dtype, double* e,
                                    unsigned long long* range, const Rs3SelectArgs& a, int n_groups, hipStream_t st,
-                                   const Rs3QProjArgs* qp) {
+                                   const Rs3QProjArgs* qp, const Rs3CopyArgs* copy) {
   if (qp && !qproj_ok(C, dtype, qp)) return hipErrorInvalidValue;
   const Rs3QProjArgs q = qp ? *qp : Rs3QProjArgs{};
   // blocks beside the energies: one per group, or one per four mask rows
   const int n_more = a.row_box ? (a.n_obj * a.m + 3) / 4 : n_groups;
+  Rs3CopyArgs cp = copy ? *copy : Rs3CopyArgs{};
+  cp.blocks = cp.Y && cp.copies > 1 ? (int)std::min<int64_t>(1024, (cp.n_x * cp.count + 1023) / 1024) : 0;
   if (energy_wide(n_x, mn, qp)) {
     const int nbw = (mn + EW_ROWS - 1) / EW_ROWS, n_w = nbw * n_x;
-    const dim3 gw(n_w + n_more);
+    const dim3 gw(n_w + n_more + cp.blocks);
     if (dtype == RS3_BF16)
       RS3_LAUNCH(RS3_K_ENERGY, st, (k_energy_prior<bf16_t, false, true>), gw, dim3(256), 0, st, (const bf16_t*)X,
-                 x_stride, mn, C, e, range, a, nbw, n_w, q);
+                 x_stride, mn, C, e, range, a, nbw, n_w, n_more, q, cp);
     else
       RS3_LAUNCH(RS3_K_ENERGY, st, (k_energy_prior<float, false, true>), gw, dim3(256), 0, st, (const float*)X,
-                 x_stride, mn, C, e, range, a, nbw, n_w, q);
+                 x_stride, mn, C, e, range, a, nbw, n_w, n_more, q, cp);
     return hipGetLastError();
   }
   const int nbx = (mn + 63) / 64, n_e = nbx * n_x;
-  const dim3 grid(n_e + n_more);
+  const dim3 grid(n_e + n_more + cp.blocks);
   if (qp)
     RS3_LAUNCH(RS3_K_ENERGY, st, (k_energy_prior<bf16_t, true>), grid, dim3(256), 0, st, (const bf16_t*)X, x_stride,
-               mn, C, e, range, a, nbx, n_e, q);
+               mn, C, e, range, a, nbx, n_e, n_more, q, cp);
   else if (dtype == RS3_BF16)
     RS3_LAUNCH(RS3_K_ENERGY, st, k_energy_prior<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)X, x_stride, mn, C, e,
-               range, a, nbx, n_e, q);
+               range, a, nbx, n_e, n_more, q, cp);
   else
     RS3_LAUNCH(RS3_K_ENERGY, st, k_energy_prior<float>, grid, dim3(256), 0, st, (const float*)X, x_stride, mn, C, e,
-               range, a, nbx, n_e, q);
+               range, a, nbx, n_e, n_more, q, cp);
   return hipGetLastError();
 }
 
