@@ -1036,7 +1036,7 @@ rs3_status rs3_close_masks(int32_t n_obj, int32_t H, int32_t W, const void* logi
   if (dt != RS3_BF16 && dt != RS3_F32) return RS3_E_INVALID;
   if (k < 1 || k > 15 || k % 2 == 0) return RS3_E_INVALID;
   if (ws_bytes < rs3_post_workspace_bytes(n_obj, H, W)) return RS3_E_INVALID;
-  return map_err(rs3_launch_close_masks(n_obj, H, W, logits, dt, k, closed, palette, ws, (hipStream_t)stream));
+  return map_err(rs3_launch_close_masks(n_obj, H, W, logits, dt, k, closed, palette, (hipStream_t)stream));
 }
 
 // ---- commit ----------------------------------------------------------------

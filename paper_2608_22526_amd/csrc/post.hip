@@ -5,301 +5,228 @@
 // object with the largest logit among those whose closed mask covers it
 // (lowest index on ties), 0 where none does.
 //
-// Three launches over bit-packed masks (bit x%64 of word x/64 of a row):
-//   k_post_threshold : one wave per 64-pixel word of a row: per object a
-//                      ballot of logit > 0 gives the word; the largest
-//                      logit over all objects and its object are kept.  If
-//                      that logit is > 0 the object covers the pixel (its
-//                      mask is set there and closing only adds), so it is
-//                      the palette value; such pixels need no second look.
-//   k_post_close     : one work-group per (object, 8-row tile): the bit
-//                      rows with a 2r-row halo (k = 2r+1) go to LDS; row
-//                      dilation, column dilation, row erosion and column
-//                      erosion run on whole words (shifts across the
-//                      neighbouring word); writes the closed words and,
-//                      when asked, the closed masks as bytes.
-//   k_post_palette   : one wave per word: pixels whose largest logit was
-//                      > 0 take that object; the others take the largest
-//                      logit among the objects whose closed word covers
-//                      them (those logits are read only there).
-#include "rs3_internal.h"
+// One launch, one work-group per tile of 64 x (64 - 4r) pixels (k = 2r+1),
+// which needs the masks of 2r pixels around it:
+//   1. a wave per object (and round) reads the tile's logits with its border,
+//      eight pixels per lane and load, into bits: lane y then holds row y of
+//      the 96 x 64 window (16 pixels left and right, 2r above and below);
+//   2. the closing runs in that wave's registers, without a barrier: along
+//      rows by shifts, across rows by lane shuffles, each in doubling steps
+//      (a step of at most done + 1 leaves no gap); the erosion is the dilation
+//      of the complement.  The closed rows go to LDS;
+//   3. after one barrier a thread takes eight pixels of every object: the
+//      closed bytes, and the logits of the objects that cover any of them.
+// Bound by the reads of step 1 (twice the image with the border at r = 4, from
+// L2) and three memory round trips.  Eight masks of 1024 x 1024 (26 MB in and
+// out): 17.6 us; three launches over bit words in memory (threshold, closing,
+// palette) took 21.1 us; three masks of 480 x 854 8.9 against 13.1.
+#include "device_util.h"
 
 namespace rs3 {
 
-constexpr int PC_TILE = 8;    // output rows per closing work-group
-constexpr int PC_RMAX = 7;    // largest radius (k <= 15)
-constexpr int PC_WWMAX = 64;  // words per row (W <= 4096)
-constexpr int PC_ROWS = PC_TILE + 4 * PC_RMAX;
+constexpr int PC_TX = 64;      // tile width
+constexpr int PC_HALO = 16;    // window pixels left and right of it (>= 2 * largest radius, 7)
+constexpr int PC_CH = (PC_TX + 2 * PC_HALO) / 8;   // 8-pixel chunks per window row
+constexpr int PC_WAVES = 8;
 
-__device__ __forceinline__ float logit_at(const bf16_t* p, int64_t i) { return bf2f(p[i]); }
-__device__ __forceinline__ float logit_at(const float* p, int64_t i) { return p[i]; }
-
-// grid: ceil(H*WW / 4) work-groups of 4 waves; wave -> (row, word).
+// Eight logits as they lie in memory (rows start at any element, so the loads
+// are unaligned).  No branch: the loads of a batch go out together, where loads
+// behind lane conditions wait one by one.
 template <typename T>
-__global__ __launch_bounds__(256) void k_post_threshold(const T* logits, int n_obj, int H, int W, int WW,
-                                                        uint64_t* bits, uint8_t* amax) {
+struct Raw8;
+template <>
+struct Raw8<bf16_t> {
+  u32x4 w;
+  __device__ __forceinline__ void load(const bf16_t* p) {
+    typedef u32x4 u32x4_u __attribute__((aligned(2)));
+    w = *(const RS3_GLOBAL u32x4_u*)p;
+  }
+  // near the right border: pixels past the first n repeat pixel n - 1
+  __device__ __forceinline__ void load_edge(const bf16_t* p, int n) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      w[j] = gload(p + min(2 * j, n - 1)) | (uint32_t)gload(p + min(2 * j + 1, n - 1)) << 16;
+  }
+  __device__ __forceinline__ float at(int j) const {
+    return __uint_as_float((j & 1) ? w[j >> 1] & 0xffff0000u : w[j >> 1] << 16);
+  }
+};
+template <>
+struct Raw8<float> {
+  f32x4 a, b;
+  __device__ __forceinline__ void load(const float* p) {
+    typedef f32x4 f32x4_u __attribute__((aligned(4)));
+    a = *(const RS3_GLOBAL f32x4_u*)p;
+    b = *(const RS3_GLOBAL f32x4_u*)(p + 4);
+  }
+  __device__ __forceinline__ void load_edge(const float* p, int n) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a[j] = gload(p + min(j, n - 1));
+      b[j] = gload(p + min(4 + j, n - 1));
+    }
+  }
+  __device__ __forceinline__ float at(int j) const { return j < 4 ? a[j & 3] : b[j & 3]; }
+};
+
+// Eight bytes to p (unaligned), the first n of them at the right border.
+__device__ __forceinline__ void store8(uint8_t* p, int n, uint64_t b) {
+  typedef uint64_t u64_u __attribute__((aligned(1)));
+  if (n >= 8)
+    *(RS3_GLOBAL u64_u*)p = b;
+  else
+    for (int j = 0; j < n; ++j) gstore(p + j, (uint8_t)(b >> (8 * j)));
+}
+
+// One row of the window: pixels 0..63 and 64..95.
+struct PcRow {
+  uint64_t lo;
+  uint32_t hi;
+};
+
+__device__ __forceinline__ PcRow lane_row(const PcRow& a, int src) {   // row of lane src, 0 outside the window
+  const uint32_t l = (uint32_t)__shfl((int)(uint32_t)a.lo, src), m = (uint32_t)__shfl((int)(uint32_t)(a.lo >> 32), src);
+  const uint32_t h = (uint32_t)__shfl((int)a.hi, src);
+  const bool in = src >= 0 && src < 64;
+  return PcRow{in ? (uint64_t)m << 32 | l : 0ull, in ? h : 0u};
+}
+
+// (2r+1)^2 square dilation of the window; pixels outside it are unset.
+__device__ __forceinline__ PcRow dilate(PcRow a, int r) {
   const int lane = threadIdx.x & 63;
-  const int64_t word = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (word >= (int64_t)H * WW) return;
-  const int y = (int)(word / WW), w = (int)(word - (int64_t)y * WW);
-  const int x = 64 * w + lane;
-  const bool in = x < W;
+  for (int done = 0; done < r;) {
+    const int s = min(done + 1, r - done);
+    const uint64_t lo = a.lo, hi = a.hi;
+    a.lo = lo | lo << s | lo >> s | hi << (64 - s);
+    a.hi = (uint32_t)(hi | hi << s | hi >> s | lo >> (64 - s));
+    done += s;
+  }
+  for (int done = 0; done < r;) {
+    const int s = min(done + 1, r - done);
+    const PcRow u = lane_row(a, lane - s), d = lane_row(a, lane + s);
+    a.lo |= u.lo | d.lo;
+    a.hi |= u.hi | d.hi;
+    done += s;
+  }
+  return a;
+}
+
+// grid (ceil(W / 64), ceil(H / (64 - 4r))), block 64 * nw.  closed, palette:
+// optional.  dyn: [n_obj][64] closed rows of the tile.
+template <typename T>
+__global__ __launch_bounds__(64 * PC_WAVES, 4) void k_post_close(const T* logits, int n_obj, int H, int W, int r,
+                                                              uint8_t* closed, uint8_t* palette) {
+  extern __shared__ __attribute__((aligned(16))) uint64_t rows[];   // [n_obj][64]
+  __shared__ __attribute__((aligned(16))) uint8_t win[PC_WAVES][64][16];   // a wave's window: 12 bytes of each row
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const int ty = 64 - 4 * r;   // tile rows: lanes 2r .. 64-2r-1
+  const int x0 = blockIdx.x * PC_TX, y0 = blockIdx.y * ty;
   const int64_t plane = (int64_t)H * W;
-  const int64_t px = (int64_t)y * W + (in ? x : W - 1);
-  float best = -INFINITY;
-  int arg = 0;
-  for (int o = 0; o < n_obj; ++o) {
-    const float v = logit_at(logits, (int64_t)o * plane + px);
-    const unsigned long long b = __ballot(in && v > 0.f);
-    if (lane == 0) bits[((int64_t)o * H + y) * WW + w] = b;
-    if (v > best) {
-      best = v;
-      arg = o;
-    }
+  // this lane's row of the window and the pixels of it inside the image
+  const int y = y0 - 2 * r + lane;
+  PcRow inside = {0ull, 0u};
+  if (y >= 0 && y < H) {
+    const int n = min(W - (x0 - PC_HALO), 96);   // window pixels left of the right border
+    inside.lo = n >= 64 ? ~0ull : (1ull << n) - 1ull;
+    inside.hi = n >= 96 ? ~0u : n > 64 ? (1u << (n - 64)) - 1u : 0u;
+    if (x0 == 0) inside.lo &= ~0ull << PC_HALO;
   }
-  if (in) amax[px] = best > 0.f ? (uint8_t)arg : (uint8_t)0xFF;
-}
-
-// Row word w of `row` (WW words, bits past W already at `pad`) shifted so
-// that bit x takes bit x - d (d > 0) or x + |d| (d < 0); words outside the
-// row read as `pad_word`.
-__device__ __forceinline__ uint64_t shifted(const uint64_t* row, int WW, int w, int d, uint64_t pad_word) {
-  const uint64_t cur = row[w];
-  if (d > 0) {
-    const uint64_t lo = w > 0 ? row[w - 1] : pad_word;
-    return (cur << d) | (lo >> (64 - d));
-  }
-  const int e = -d;
-  const uint64_t hi = w + 1 < WW ? row[w + 1] : pad_word;
-  return (cur >> e) | (hi << (64 - e));
-}
-
-// Sixteen mask bits -> sixteen 0/1 bytes.
-__device__ __forceinline__ u32x4 bits_to_bytes16(uint32_t h) {
-  auto nib = [](uint32_t n) { return (n & 1u) | ((n & 2u) << 7) | ((n & 4u) << 14) | ((n & 8u) << 21); };
-  return u32x4{nib(h & 15u), nib((h >> 4) & 15u), nib((h >> 8) & 15u), nib((h >> 12) & 15u)};
-}
-
-// grid (ceil(H / PC_TILE), n_obj), block 256.
-__global__ __launch_bounds__(256) void k_post_close(const uint64_t* bits, int H, int W, int WW, int r,
-                                                    uint64_t* closed_bits, uint8_t* closed, int vec16) {
-  __shared__ uint64_t A[PC_ROWS * PC_WWMAX];
-  __shared__ uint64_t B[PC_ROWS * PC_WWMAX];
-  const int o = blockIdx.y, tid = threadIdx.x;
-  const int y0 = blockIdx.x * PC_TILE, y1 = min(H, y0 + PC_TILE);
-  const int ya = max(0, y0 - 2 * r), yb = min(H, y1 + 2 * r);   // rows held: [ya, yb)
-  const int nr = yb - ya;
-  const int rem = W - 64 * (WW - 1);
-  const uint64_t tail = rem == 64 ? 0ull : ~0ull << rem;   // bits past W in the last word
-  const uint64_t* src = bits + (int64_t)o * H * WW;
-  for (int i = tid; i < nr * WW; i += 256) A[i] = src[(int64_t)ya * WW + i];
-  __syncthreads();
-  // row dilation (outside unset) A -> B
-  for (int i = tid; i < nr * WW; i += 256) {
-    const int rr = i / WW, w = i - rr * WW;
-    const uint64_t* row = A + rr * WW;
-    uint64_t v = row[w];
-    for (int d = 1; d <= r; ++d) v |= shifted(row, WW, w, d, 0ull) | shifted(row, WW, w, -d, 0ull);
-    if (w == WW - 1) v &= ~tail;
-    B[i] = v;
-  }
-  __syncthreads();
-  // column dilation B -> A, rows [y0 - r, y1 + r) of the image; the bits
-  // past W are set here, so that the erosion counts them as set
-  const int ca = max(0, y0 - r), cb = min(H, y1 + r);
-  for (int i = tid; i < (cb - ca) * WW; i += 256) {
-    const int y = ca + i / WW, w = i - (i / WW) * WW;
-    uint64_t v = 0;
-    for (int yy = max(0, y - r); yy <= min(H - 1, y + r); ++yy) v |= B[(yy - ya) * WW + w];
-    A[(y - ya) * WW + w] = w == WW - 1 ? (v | tail) : v;
-  }
-  __syncthreads();
-  // row erosion (outside set: words past the row read as all set) A -> B
-  for (int i = tid; i < (cb - ca) * WW; i += 256) {
-    const int y = ca + i / WW, w = i - (i / WW) * WW;
-    const uint64_t* row = A + (y - ya) * WW;
-    uint64_t v = row[w];
-    for (int d = 1; d <= r; ++d) v &= shifted(row, WW, w, d, ~0ull) & shifted(row, WW, w, -d, ~0ull);
-    B[(y - ya) * WW + w] = w == WW - 1 ? (v & ~tail) : v;
-  }
-  __syncthreads();
-  // column erosion (outside set) B -> output rows [y0, y1)
-  uint64_t* dstb = closed_bits + (int64_t)o * H * WW;
-  for (int i = tid; i < (y1 - y0) * WW; i += 256) {
-    const int y = y0 + i / WW, w = i - (i / WW) * WW;
-    uint64_t v = ~0ull;
-    for (int yy = max(0, y - r); yy <= min(H - 1, y + r); ++yy) v &= B[(yy - ya) * WW + w];
-    if (w == WW - 1) v &= ~tail;
-    dstb[(int64_t)y * WW + w] = v;
-    if (closed) {
-      uint8_t* dst = closed + ((int64_t)o * H + y) * W + 64 * w;
-      const int nb = min(64, W - 64 * w);
-      if (vec16) {   // W % 16 == 0 and a 16-byte aligned output
-        for (int c = 0; c < nb / 16; ++c) *(u32x4*)(dst + 16 * c) = bits_to_bytes16((uint32_t)(v >> (16 * c)) & 0xffffu);
-      } else {
-        for (int b = 0; b < nb; ++b) dst[b] = (uint8_t)((v >> b) & 1ull);
+  for (int o = wave; o < n_obj; o += nw) {
+    const T* L = logits + o * plane;
+    // chunk q = lane + 64 i: window row q / 12, pixels 8 (q % 12) .. +7.  Rows
+    // and chunks outside the image read the nearest ones inside (their bits
+    // are masked below); a chunk that crosses the right border reads the
+    // row's last eight pixels and shifts them into place.
+    constexpr int NB = sizeof(T) == 2 ? PC_CH : PC_CH / 2;   // chunks in flight (48 registers)
+#pragma unroll
+    for (int i0 = 0; i0 < PC_CH; i0 += NB) {
+      Raw8<T> v[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int q = lane + 64 * (i0 + i), row = q / PC_CH, c = q - row * PC_CH;
+        const int yy = min(max(y0 - 2 * r + row, 0), H - 1), xx = x0 - PC_HALO + 8 * c;
+        if (W >= 8)
+          v[i].load(L + (int64_t)yy * W + min(max(xx, 0), W - 8));
+        else
+          v[i].load_edge(L + (int64_t)yy * W, W);
+      }
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int q = lane + 64 * (i0 + i), row = q / PC_CH, c = q - row * PC_CH;
+        const int xx = x0 - PC_HALO + 8 * c;
+        uint32_t b = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b |= (v[i].at(j) > 0.f ? 1u : 0u) << j;
+        win[wave][row][c] = (uint8_t)(b >> min(max(W >= 8 ? xx - (W - 8) : xx, 0), 8));
       }
     }
+    // the window is written and read by this wave alone
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const u32x4 w = *(const u32x4*)win[wave][lane];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    PcRow a = dilate(PcRow{((uint64_t)w[1] << 32 | w[0]) & inside.lo, w[2] & inside.hi}, r);
+    // erosion with the pixels outside the image set: their complement is unset
+    a = dilate(PcRow{~a.lo & inside.lo, ~a.hi & inside.hi}, r);
+    a.lo = ~a.lo & inside.lo;
+    a.hi = ~a.hi & inside.hi;
+    rows[o * 64 + lane] = a.lo >> PC_HALO | (uint64_t)a.hi << (64 - PC_HALO);   // the tile's 64 pixels
   }
-}
-
-// grid: ceil(H*WW / 4), block 256 (wave -> (row, word)).
-template <typename T>
-__global__ __launch_bounds__(256) void k_post_palette(const T* logits, int n_obj, int H, int W, int WW,
-                                                      const uint64_t* closed_bits, const uint8_t* amax,
-                                                      uint8_t* palette) {
-  const int lane = threadIdx.x & 63;
-  const int64_t word = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (word >= (int64_t)H * WW) return;
-  const int y = (int)(word / WW), w = (int)(word - (int64_t)y * WW);
-  const int x = 64 * w + lane;
-  if (x >= W) return;
-  const int64_t plane = (int64_t)H * W, px = (int64_t)y * W + x;
-  const uint8_t a = amax[px];
-  if (a != 0xFF) {
-    palette[px] = (uint8_t)(a + 1);
-    return;
-  }
-  float best = -INFINITY;
-  int arg = -1;
-  for (int o = 0; o < n_obj; ++o) {
-    const uint64_t cw = closed_bits[((int64_t)o * H + y) * WW + w];
-    if ((cw >> lane) & 1ull) {
-      const float v = logit_at(logits, (int64_t)o * plane + px);
-      if (arg < 0 || v > best) {
-        best = v;
-        arg = o;
-      }
-    }
-  }
-  palette[px] = (uint8_t)(arg + 1);
-}
-
-// Eight pixels per lane (rows of W % 8 == 0): one wave covers 512 pixels
-// (eight words) of a row.  Each lane loads its 8 logits with 16-byte loads,
-// forms 8 mask bits, and the 8 lanes of a word OR their bytes together.
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, float* v);
-template <>
-__device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float* v) {
-  const u32x4 w = *(const u32x4*)p;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    v[2 * j] = __uint_as_float(w[j] << 16);
-    v[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-  }
-}
-template <>
-__device__ __forceinline__ void load8<float>(const float* p, float* v) {
-  const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 4);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    v[j] = a[j];
-    v[4 + j] = b[j];
-  }
-}
-
-// grid: ceil(H*G8 / 4) work-groups of 4 waves, G8 = ceil(WW / 8).
-template <typename T>
-__global__ __launch_bounds__(256) void k_post_threshold8(const T* logits, int n_obj, int H, int W, int WW, int G8,
-                                                         uint64_t* bits, uint8_t* amax) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wid >= (int64_t)H * G8) return;
-  const int y = (int)(wid / G8), gq = (int)(wid - (int64_t)y * G8);
-  const int x0 = 512 * gq + 8 * lane;
-  const bool in = x0 < W;   // W % 8 == 0: a lane's 8 pixels are all in or all out
-  const int q = 8 * gq + (lane >> 3);
-  const int64_t plane = (int64_t)H * W, px = (int64_t)y * W + (in ? x0 : 0);
-  float best[8];
-  int arg[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    best[j] = -INFINITY;
-    arg[j] = 0;
-  }
-  for (int o = 0; o < n_obj; ++o) {
-    float v[8];
-    load8<T>(logits + (int64_t)o * plane + px, v);
-    uint32_t b8 = 0;
+  __syncthreads();
+  const bool edge = x0 + PC_TX > W;   // the last tile of a row
+  for (int q = tid; q < 8 * ty; q += 64 * nw) {
+    const int row = q >> 3, c = q & 7, yy = y0 + row, xx = x0 + 8 * c;
+    if (yy >= H || xx >= W) continue;
+    const int n = W - xx;
+    const int64_t px = (int64_t)yy * W + xx;
+    // pos: the object with the largest positive logit, which has the pixel
+    // wherever there is one (its mask, and so its closed mask, covers it);
+    // any: the largest logit among the covering objects, for filled holes.
+    // Objects that cover no pixel of the wave's eight rows are passed over.
+    float pos[8], any[8];
+    int parg[8], aarg[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      b8 |= (v[j] > 0.f ? 1u : 0u) << j;
-      if (v[j] > best[j]) {
-        best[j] = v[j];
-        arg[j] = o;
-      }
-    }
-    uint64_t word = in ? (uint64_t)b8 << (8 * (lane & 7)) : 0ull;
-    word |= __shfl_xor(word, 1);
-    word |= __shfl_xor(word, 2);
-    word |= __shfl_xor(word, 4);
-    if ((lane & 7) == 0 && q < WW) bits[((int64_t)o * H + y) * WW + q] = word;
-  }
-  if (in) {
-    uint64_t a = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) a |= (uint64_t)(best[j] > 0.f ? (uint32_t)arg[j] : 0xffu) << (8 * j);
-    *(uint64_t*)(amax + px) = a;
-  }
-}
-
-// grid: ceil(H*G8 / 4), block 256 (8 pixels per lane, W % 8 == 0).
-template <typename T>
-__global__ __launch_bounds__(256) void k_post_palette8(const T* logits, int n_obj, int H, int W, int WW, int G8,
-                                                       const uint64_t* closed_bits, const uint8_t* amax,
-                                                       uint8_t* palette) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wid >= (int64_t)H * G8) return;
-  const int y = (int)(wid / G8), gq = (int)(wid - (int64_t)y * G8);
-  const int x0 = 512 * gq + 8 * lane;
-  if (x0 >= W) return;
-  const int64_t plane = (int64_t)H * W, px = (int64_t)y * W + x0;
-  const uint64_t a8 = *(const uint64_t*)(amax + px);
-  uint64_t out = 0;
-  uint32_t need = 0;   // pixels whose largest logit is not > 0
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t a = (uint32_t)(a8 >> (8 * j)) & 0xffu;
-    if (a != 0xffu)
-      out |= (uint64_t)(a + 1) << (8 * j);
-    else
-      need |= 1u << j;
-  }
-  if (need) {
-    const int q = x0 >> 6, sh = x0 & 63;
-    float best[8];
-    int arg[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      best[j] = -INFINITY;
-      arg[j] = -1;
+      pos[j] = any[j] = 0.f;
+      parg[j] = aarg[j] = -1;
     }
     for (int o = 0; o < n_obj; ++o) {
-      const uint32_t cb = (uint32_t)(closed_bits[((int64_t)o * H + y) * WW + q] >> sh) & need;
-      if (!cb) continue;
+      const uint32_t b = (uint32_t)(rows[o * 64 + 2 * r + row] >> (8 * c)) & 0xffu;
+      if (closed) {   // bit j -> byte j
+        const uint32_t lo4 = (b & 1u) | (b & 2u) << 7 | (b & 4u) << 14 | (b & 8u) << 21;
+        const uint32_t hi4 = (b >> 4 & 1u) | (b & 32u) << 3 | (b & 64u) << 10 | (b & 128u) << 17;
+        store8(closed + o * plane + px, n, lo4 | (uint64_t)hi4 << 32);
+      }
+      if (!palette || !__any(b != 0u)) continue;
+      Raw8<T> v;
+      if (edge)
+        v.load_edge(logits + o * plane + px, n);
+      else
+        v.load(logits + o * plane + px);
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if ((cb >> j) & 1u) {
-          const float v = logit_at(logits, (int64_t)o * plane + px + j);
-          if (arg[j] < 0 || v > best[j]) {
-            best[j] = v;
-            arg[j] = o;
-          }
-        }
+      for (int j = 0; j < 8; ++j) {
+        const float x = v.at(j);
+        parg[j] = x > pos[j] ? o : parg[j];
+        pos[j] = x > pos[j] ? x : pos[j];
+        const bool f = (b >> j & 1u) && (aarg[j] < 0 || x > any[j]);
+        aarg[j] = f ? o : aarg[j];
+        any[j] = f ? x : any[j];
+      }
     }
+    if (!palette) continue;
+    uint64_t out = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if ((need >> j) & 1u) out |= (uint64_t)(arg[j] + 1) << (8 * j);
+    for (int j = 0; j < 8; ++j) out |= (uint64_t)(uint32_t)((parg[j] >= 0 ? parg[j] : aarg[j]) + 1) << (8 * j);
+    store8(palette + px, n, out);
   }
-  *(uint64_t*)(palette + px) = out;
 }
 
 }  // namespace rs3
 
 using namespace rs3;
 
+// What rs3_close_masks asks of its caller's workspace (two sets of bit words
+// and a byte per pixel).  The launch keeps its words in LDS and leaves the
+// workspace alone; the contract stays.
 size_t rs3_post_workspace_bytes(int n_obj, int H, int W) {
   const size_t WW = (size_t)(W + 63) / 64;
   const size_t words = (size_t)n_obj * H * WW * 8;
@@ -307,48 +234,16 @@ size_t rs3_post_workspace_bytes(int n_obj, int H, int W) {
 }
 
 hipError_t rs3_launch_close_masks(int n_obj, int H, int W, const void* logits, int dtype, int k, uint8_t* closed,
-                                  uint8_t* palette, void* ws, hipStream_t st) {
-  const int WW = (W + 63) / 64, G8 = (WW + 7) / 8;
-  const size_t words = (size_t)n_obj * H * WW * 8;
-  uint64_t* bits = (uint64_t*)ws;
-  uint64_t* cbits = (uint64_t*)((uint8_t*)ws + ((words + 255) & ~(size_t)255));
-  uint8_t* amax = (uint8_t*)ws + 2 * ((words + 255) & ~(size_t)255);
-  const int64_t nwords = (int64_t)H * WW, ngroups = (int64_t)H * G8;
-  // eight pixels per lane where rows and the logits are 16-byte aligned
-  const bool wide = W % 8 == 0 && ((uintptr_t)logits & 15) == 0;
-  const dim3 g1((unsigned)((nwords + 3) / 4)), g8((unsigned)((ngroups + 3) / 4));
-  const bool bf = dtype == RS3_BF16;
-  if (wide && bf)
-    hipLaunchKernelGGL(k_post_threshold8<bf16_t>, g8, dim3(256), 0, st, (const bf16_t*)logits, n_obj, H, W, WW, G8,
-                       bits, amax);
-  else if (wide)
-    hipLaunchKernelGGL(k_post_threshold8<float>, g8, dim3(256), 0, st, (const float*)logits, n_obj, H, W, WW, G8,
-                       bits, amax);
-  else if (bf)
-    hipLaunchKernelGGL(k_post_threshold<bf16_t>, g1, dim3(256), 0, st, (const bf16_t*)logits, n_obj, H, W, WW, bits,
-                       amax);
+                                  uint8_t* palette, hipStream_t st) {
+  const int r = k / 2, ty = 64 - 4 * r;
+  const int nw = n_obj < 4 ? 4 : n_obj < PC_WAVES ? n_obj : PC_WAVES;   // four for the palette's sake
+  const dim3 grid((W + PC_TX - 1) / PC_TX, (H + ty - 1) / ty);
+  const size_t lds = (size_t)n_obj * 64 * 8;
+  if (dtype == RS3_BF16)
+    hipLaunchKernelGGL(k_post_close<bf16_t>, grid, dim3(64 * nw), lds, st, (const bf16_t*)logits, n_obj, H, W, r,
+                       closed, palette);
   else
-    hipLaunchKernelGGL(k_post_threshold<float>, g1, dim3(256), 0, st, (const float*)logits, n_obj, H, W, WW, bits,
-                       amax);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int vec16 = closed && W % 16 == 0 && ((uintptr_t)closed & 15) == 0;
-  hipLaunchKernelGGL(k_post_close, dim3((unsigned)((H + PC_TILE - 1) / PC_TILE), (unsigned)n_obj), dim3(256), 0, st,
-                     bits, H, W, WW, k / 2, cbits, closed, vec16);
-  e = hipGetLastError();
-  if (e != hipSuccess || !palette) return e;
-  const bool wide_out = wide && ((uintptr_t)palette & 7) == 0;
-  if (wide_out && bf)
-    hipLaunchKernelGGL(k_post_palette8<bf16_t>, g8, dim3(256), 0, st, (const bf16_t*)logits, n_obj, H, W, WW, G8,
-                       cbits, amax, palette);
-  else if (wide_out)
-    hipLaunchKernelGGL(k_post_palette8<float>, g8, dim3(256), 0, st, (const float*)logits, n_obj, H, W, WW, G8, cbits,
-                       amax, palette);
-  else if (bf)
-    hipLaunchKernelGGL(k_post_palette<bf16_t>, g1, dim3(256), 0, st, (const bf16_t*)logits, n_obj, H, W, WW, cbits,
-                       amax, palette);
-  else
-    hipLaunchKernelGGL(k_post_palette<float>, g1, dim3(256), 0, st, (const float*)logits, n_obj, H, W, WW, cbits,
-                       amax, palette);
+    hipLaunchKernelGGL(k_post_close<float>, grid, dim3(64 * nw), lds, st, (const float*)logits, n_obj, H, W, r, closed,
+                       palette);
   return hipGetLastError();
 }

@@ -368,7 +368,7 @@ hipError_t rs3_launch_write_keepset(const uint8_t* seed, int n_obj, int m, int n
 // Closure of decoded masks and the palette (see rs3_close_masks).
 size_t rs3_post_workspace_bytes(int n_obj, int H, int W);
 hipError_t rs3_launch_close_masks(int n_obj, int H, int W, const void* logits, int dtype, int k, uint8_t* closed,
-                                  uint8_t* palette, void* ws, hipStream_t st);
+                                  uint8_t* palette, hipStream_t st);
 // Fills the axial rotary table (see rs3_layer_set_rope_axial).
 hipError_t rs3_launch_rope_axial(float* table, int m, int n, int d_h, double theta, hipStream_t st);
 // While profiling is on: the next free pair of the event pool for a launch

@@ -85,3 +85,19 @@ def test_closed_masks_drive_the_next_selection():
     assert np.array_equal(_host(prior).astype(bool), priors)
     exp_tracks = np.array([tr.as_list() for tr in r.orc.tracks], dtype=np.int32)
     assert np.array_equal(r.sess.track.export(), exp_tracks)
+
+
+@pytest.mark.parametrize("n_obj,H,W,k,dtype", [
+    (1, 49, 64, 9, "bf16"),      # one tile and one row of the next
+    (9, 48, 129, 9, "bf16"),     # a second round of objects, one column in the last tile
+    (2, 73, 71, 15, "bf16"),     # the widest square, unaligned rows
+    (3, 61, 67, 7, "f32"),
+    (64, 20, 17, 9, "bf16"),     # the most objects, rows narrower than the border
+    (2, 64, 4096, 5, "f32"),
+    (1, 1, 1, 15, "bf16")])
+def test_tile_borders(n_obj, H, W, k, dtype):
+    L = make_decoder_logits(n_obj, H, W, seed=W * 7 + k, dtype=dtype, area=(0.2, 0.8), hole_p=0.1)
+    closed, pal = _close_gpu(L, dtype, k)
+    exp_closed, exp_pal = oracle.close_masks(storage_to_f64(L, dtype), k)
+    assert np.array_equal(closed, exp_closed)
+    assert np.array_equal(pal, exp_pal)
