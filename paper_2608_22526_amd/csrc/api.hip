@@ -102,6 +102,17 @@ int auto_splits(int n_obj, int H, int n_qt, double kv_bytes) {
   int S = groups / (n_obj * H);
   const double s_l2 = kv_bytes / L2_SPLIT_BYTES;
   if (s_l2 > S) S = s_l2 > 4096.0 ? 4096 : (int)s_l2 + 1;
+  // A launch of one to four work-groups per CU takes as long as its fullest
+  // CUs: down to the whole number of work-groups per CU where that keeps 70 %
+  // of the splits (one object of 1,228 queries against 42 k keys: 24 instead
+  // of 33 splits, 55 against 61 us per read).
+  if (n_qt > 0 && S > 0) {
+    const int per = n_qt * ((n_obj * H * S + 7) / 8), k = per / 32;   // work-groups per XCD, and per CU
+    if (k >= 1 && k < 4) {
+      const int fit = 8 * (32 * k / n_qt) / (n_obj * H);
+      if (fit < S && 10 * fit >= 7 * S) S = fit;
+    }
+  }
   const int cap = max_auto_splits(H);
   if (S > cap) S = cap;
   if (S < 1) S = 1;
