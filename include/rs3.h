@@ -292,7 +292,7 @@ rs3_status rs3_commit(rs3_bank* const* banks /*[host]*/, int32_t n_obj, const rs
  * the merge reads the attention partials, X and W_o and writes Y, the commit
  * writes the banks, so their work-groups run side by side (Algorithm 1 writes
  * a frame to memory right after its readout).  Calls whose two parts come to
- * more than 1,024 work-groups (many objects) run them as two launches, which
+ * more than 768 work-groups (many objects) run them as two launches, which
  * fit the chip better at that size.  Both argument sets are checked
  * before any device work; either failing returns RS3_E_INVALID with no state
  * changed.  When the selection list and the commit both find device errors,

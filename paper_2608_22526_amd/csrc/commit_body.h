@@ -537,6 +537,11 @@ __device__ __forceinline__ void commit_block(const Rs3CommitArgs& a, int o, int 
     before = c0 < mn ? c0 : mn;
     total = mn;
   }
+  // a work-group past the kept rows is done: most are, since the launch covers
+  // every cell and a frame keeps a quarter of them (waiting for the placement
+  // too they held the CUs of a frame of eight objects 4 us longer)
+  const int parts = BF16 ? 1 : a.col_parts, rb = (y - 1) / parts, part = (y - 1) - rb * parts;
+  if (y > 0 && rb * a.rows_per_wg >= total) return;
   if (tid < 4 * f_max) sfr[tid] = fr_w;
   lds_barrier();
   if (tid < 64) {
@@ -577,7 +582,6 @@ __device__ __forceinline__ void commit_block(const Rs3CommitArgs& a, int o, int 
   // kept rows [rb*rows_per_wg, (rb+1)*rows_per_wg) of the new frame, 64 per
   // round; the projections' column blocks are split over col_parts work-groups
   const int start = sh.start;
-  const int parts = BF16 ? 1 : a.col_parts, rb = (y - 1) / parts, part = (y - 1) - rb * parts;
   const int r_end = min(total, (rb + 1) * a.rows_per_wg);
   for (int r0 = rb * a.rows_per_wg; r0 < r_end; r0 += 64) {
     {   // kept cells of rows r0 .. r0+63

@@ -85,9 +85,11 @@ hipError_t rs3_fused_setup() {
 // Work-groups of the fused launch beyond which the merge and the commit run
 // as two launches: a fused work-group has the commit's 1,024 threads, whose
 // register count (126) allows one per CU, while the merge's 512-thread
-// blocks fit two per CU on their own (149 us fused against 75 + 34 us
-// separate at 64 objects of 898 selected rows).
-constexpr int FUSE_MAX_WGS = 1024;
+// blocks fit two per CU on their own.  Two rounds of work-groups are still
+// faster fused (eight objects on 30x54 grids, 432 work-groups: 222 against 257
+// us per six frames), four are not (eight on 64x64, 976: 357 against 340; 64
+// objects 149 against 75 + 34 us a frame).
+constexpr int FUSE_MAX_WGS = 768;
 
 hipError_t rs3_launch_merge_commit(const Rs3ReadoutArgs& ra, const Rs3CommitArgs& ca, int dtype, int d_kv,
                                    hipStream_t st) {

@@ -3,7 +3,7 @@ merge and the commit sharing one launch) through the C ABI against the fp64
 oracle: outputs within 2e-2 (bf16) or 1e-4 (fp32), unselected rows
 bit-identical, banks bit-exact after every fused call, for one object in
 both layer modes, eight objects with per-object lists and out-of-place
-outputs (past 1,024 work-groups, where the merge and the commit run as two
+outputs (past 768 work-groups, where the merge and the commit run as two
 launches), fp32 outputs, a rotary layer, the fp32 path (no merge launch), a frame
 with an empty selection, and forced key-split counts from 1 to 100."""
 from dataclasses import replace
@@ -76,7 +76,7 @@ def test_fused_forced_splits(absorb, n_splits):
 @pytest.mark.parametrize("n_obj,two", [(1, False), (2, False), (8, True)])
 def test_fused_launch_shape(n_obj, two):
     # The merge and the commit share one launch while the two parts come to
-    # at most 1,024 work-groups, else run as the readout's merge launch and
+    # at most 768 work-groups, else run as the readout's merge launch and
     # the commit launch; both shapes against the oracle, banks bit-exact.
     # At max_sel 1228 on 64x64 grids: 77 merge blocks (16 rows) and 65 commit
     # blocks per object, 1,136 at eight objects.
