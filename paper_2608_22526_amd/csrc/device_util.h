@@ -73,11 +73,23 @@ __device__ __forceinline__ void keep_s(const T& v) {
   asm volatile("" ::"s"(v));
 }
 
-// Work-group blk of `blocks` (256 threads) of a grid copy: four chunks per
-// thread and round, read once and written to every copy.
-__device__ __forceinline__ void copy_block(const Rs3CopyArgs& c, int blk, int blocks) {
+// Work-group blk of c.blocks (256 threads) of a grid copy: four chunks per
+// thread and round, read once and written to up to COPY_GROUP output grids
+// (more of them go to further work-groups: a small grid shared by many objects
+// would otherwise be written by a few CUs).
+constexpr int COPY_GROUP = 4;
+inline int copy_blocks(const Rs3CopyArgs& c, int most) {
+  const int64_t rounds = (c.n_x * c.count + 1023) / 1024, groups = (c.copies + COPY_GROUP - 1) / COPY_GROUP;
+  const int64_t per = most / groups < 1 ? 1 : most / groups;
+  return (int)((rounds < per ? rounds : per) * groups);
+}
+
+__device__ __forceinline__ void copy_block(const Rs3CopyArgs& c, int blk) {
   const int64_t total = c.n_x * c.count;
-  for (int64_t i0 = (int64_t)blk * 1024 + threadIdx.x; i0 < total; i0 += (int64_t)blocks * 1024) {
+  const int groups = (c.copies + COPY_GROUP - 1) / COPY_GROUP, cg = blk % groups;
+  const int p0 = cg * COPY_GROUP, p1 = min(p0 + COPY_GROUP, c.copies);
+  for (int64_t i0 = (int64_t)(blk / groups) * 1024 + threadIdx.x; i0 < total;
+       i0 += (int64_t)(c.blocks / groups) * 1024) {
     u32x4 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -90,7 +102,7 @@ __device__ __forceinline__ void copy_block(const Rs3CopyArgs& c, int blk, int bl
       if (i >= total) break;
       const int64_t xi = c.n_x == 1 ? 0 : i / c.count;
       u32x4* y = (u32x4*)c.Y + xi * c.y_stride + (i - xi * c.count);
-      for (int p = 0; p < c.copies; ++p) gstore(y + p * c.y_stride, v[k]);
+      for (int p = p0; p < p1; ++p) gstore(y + p * c.y_stride, v[k]);
     }
   }
 }

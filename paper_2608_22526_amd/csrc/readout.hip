@@ -30,7 +30,7 @@ namespace rs3 {
 // memory round trip, and the scatter comes later).
 __global__ __launch_bounds__(256) void k_qproj(Rs3ReadoutArgs a, int n_q, Rs3CopyArgs cp) {
   if ((int)blockIdx.x >= n_q) {
-    copy_block(cp, blockIdx.x - n_q, cp.blocks);
+    copy_block(cp, blockIdx.x - n_q);
     return;
   }
   const int nr = (a.max_sel + 63) / 64, q0 = blockIdx.x / a.n_obj;
@@ -1081,7 +1081,7 @@ __global__ __launch_bounds__(256) void k_copy_grid(const InT* X, int64_t x_strid
 }
 
 // The same for rows that keep their type.
-__global__ __launch_bounds__(256) void k_copy_grid16(Rs3CopyArgs c) { copy_block(c, blockIdx.x, c.blocks); }
+__global__ __launch_bounds__(256) void k_copy_grid16(Rs3CopyArgs c) { copy_block(c, blockIdx.x); }
 
 }  // namespace rs3
 
@@ -1145,7 +1145,7 @@ hipError_t rs3_launch_readout(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, i
   const bool beside = a.max_sel > 0 && dtype == RS3_BF16 && !attn_projects(a);
   Rs3CopyArgs cp = rs3_grid_copy(a, dtype);
   if (a.copied) cp.Y = nullptr;
-  cp.blocks = cp.Y ? (int)std::min<int64_t>(2048, (cp.n_x * cp.count + 1023) / 1024) : 0;
+  cp.blocks = cp.Y ? copy_blocks(cp, 2048) : 0;
   if (cp.Y && !beside) {
     RS3_LAUNCH(RS3_K_COPY, st, k_copy_grid16, dim3(cp.blocks), dim3(256), 0, st, cp);
     hipError_t e = hipGetLastError();

@@ -16,6 +16,8 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("m,n,C,n_obj,shared,dtype,rope", [
     (24, 20, 64, 1, True, "bf16", False),     # short last energy block
     (24, 20, 64, 3, True, "bf16", True),      # one grid to three objects (rotary: projection launch)
+    (40, 40, 64, 6, True, "bf16", False),     # more outputs than one copy work-group writes, short last group
+    (33, 31, 128, 64, True, "bf16", True),
     (64, 64, 64, 16, False, "bf16", False),   # the wide energy form, a grid each
     (100, 41, 72, 64, False, "f32", False),   # wide form, short last column slice and row block
     (70, 9, 256, 2, False, "bf16", False),    # mask rows beside, a grid each
