@@ -49,6 +49,7 @@ rs3_status ensure_setup() {
   if (setup_done) return RS3_OK;
   hipError_t e = rs3_readout_setup();
   if (e == hipSuccess) e = rs3_attn_tile_setup();
+  if (e == hipSuccess) e = rs3_attend_setup();
   if (e == hipSuccess) e = rs3_readout_f32_setup();
   if (e == hipSuccess) e = rs3_select_setup();
   if (e == hipSuccess) e = rs3_commit_setup();

@@ -4,8 +4,10 @@
 // bf16: the tensors are laid out as a one-frame bank in the caller's
 // workspace (k_attend_prep), the readout's split-KV attention kernel runs on
 // it unchanged, and k_attend_merge combines the key splits into fp32 O.
-// fp32: k_attend_f32, one work-group per query row, FMA loops.
-#include "rs3_internal.h"
+// fp32: k_attend_f32_tile, 32 queries of a head per work-group on the matrix
+// cores; k_attend_f32, one work-group per query row and FMA loops, for head
+// widths outside {32, 64, 128}.
+#include "device_util.h"
 
 namespace rs3 {
 
@@ -116,7 +118,124 @@ __global__ __launch_bounds__(256) void k_attend_merge(Rs3ReadoutArgs a, int SA, 
   *(f32x4*)(out + 4) = f32x4{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};
 }
 
-// fp32: grid n_q, block 256; per head, online softmax over 64-key tiles.
+// fp32 on the matrix cores: grid (ceil(n_q/32), H), NW waves, no workspace.  The
+// waves own the same 32 queries of one head and take the 32-key groups w, w +
+// NW, ...; as in k_attn_f32 the logits are computed transposed and the weights
+// feed the value product from their registers, accumulator register r holding
+// keys 8*(r/4) + 4*(lane/32) + r%4.  Keys and values come straight from the
+// caller's rows: a key row per lane in 16-byte chunks, the values of one key and
+// 32 channels per load.  Keys past n_kv re-read the last one with weight 0.  The
+// waves' states merge in LDS.  Bound by the latency of the loads (few waves per
+// work-group, their loads of one 32-key group in flight); 173 queries, 723 keys,
+// four heads of 64: 628 us with a work-group per query, 23 us here; 2,048 x 2,048,
+// four heads of 128: 5,727 and 111 us (77 TFLOP/s); 4 x 7,000, one head of 64:
+// 1,478 and 158 us.
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW) void k_attend_f32_tile(const float* Q, const float* K, const float* V, int n_q,
+                                                             int64_t n_kv, int H, float qscale, float* O) {
+  constexpr int OP = DH + 4;
+  extern __shared__ __attribute__((aligned(16))) float xo[];   // [NW][32][OP], then (m, l) [NW][32][2]
+  const int h = blockIdx.y, row0 = blockIdx.x * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, l31 = lane & 31;
+  const int64_t D = (int64_t)H * DH;
+  const float* qp = Q + min(row0 + l31, n_q - 1) * D + h * DH + 4 * g;
+  f32x4 q[DH / 8];
+#pragma unroll
+  for (int i = 0; i < DH / 8; ++i) q[i] = gload((const f32x4*)(qp + 8 * i)) * qscale;
+  f32x16 acc[DH / 32];
+#pragma unroll
+  for (int dt = 0; dt < DH / 32; ++dt) acc[dt] = f32x16{};
+  float m_run = -INFINITY, l_run = 0.f;
+  for (int64_t j0 = 32 * wave; j0 < n_kv; j0 += 32 * NW) {
+    const int64_t jk = j0 + l31 < n_kv ? j0 + l31 : n_kv - 1;
+    const float* kp = K + jk * D + h * DH + 4 * g;
+    f32x16 s0 = {}, s1 = {};   // two chains: shorter sums
+    constexpr int KB = DH / 8 < 8 ? DH / 8 : 8;
+#pragma unroll
+    for (int i0 = 0; i0 < DH / 8; i0 += KB) {
+      f32x4 k[KB];
+#pragma unroll
+      for (int i = 0; i < KB; ++i) k[i] = gload((const f32x4*)(kp + 8 * (i0 + i)));
+#pragma unroll
+      for (int i = 0; i < KB; i += 2) {
+        s0 = mfma32f(k[i], q[i0 + i], s0);
+        s1 = mfma32f(k[i + 1], q[i0 + i + 1], s1);
+      }
+    }
+    f32x16 sc = s0 + s1;
+    if (n_kv - j0 < 32) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (c_row(r, lane) >= (int)(n_kv - j0)) sc[r] = -INFINITY;
+    }
+    float mx = sc[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    if (__any(mx > m_run)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first group
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt) acc[dt] *= alpha;
+      m_run = m_new;
+    }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;   // every logit so far -inf: weights 0
+    float ls4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      sc[r] = __builtin_amdgcn_exp2f(sc[r] - m_use);
+      ls4[r & 3] += sc[r];
+    }
+    l_run += (ls4[0] + ls4[1]) + (ls4[2] + ls4[3]);
+    const float* vp = V + h * DH + l31;
+#pragma unroll
+    for (int dt = 0; dt < DH / 32; ++dt) {
+      float v[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t j = j0 + c_row(r, lane);
+        v[r] = gload(vp + (j < n_kv ? j : n_kv - 1) * D + 32 * dt);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[r], sc[r], acc[dt], 0, 0, 0);
+    }
+  }
+  const auto ls = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+  float* xm = xo + NW * 32 * OP;
+  if (g == 0) {
+    xm[(wave * 32 + l31) * 2] = m_run;
+    xm[(wave * 32 + l31) * 2 + 1] = __uint_as_float(ls[0]) + __uint_as_float(ls[1]);
+  }
+#pragma unroll
+  for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+      *(f32x4*)(xo + (wave * 32 + l31) * OP + 32 * dt + 8 * q4 + 4 * g) =
+          f32x4{acc[dt][4 * q4], acc[dt][4 * q4 + 1], acc[dt][4 * q4 + 2], acc[dt][4 * q4 + 3]};
+  lds_barrier();
+  for (int it = tid; it < 32 * (DH / 4); it += 64 * NW) {
+    const int rr = it / (DH / 4), c = 4 * (it % (DH / 4)), row = row0 + rr;
+    if (row >= n_q) continue;
+    float M = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) M = fmaxf(M, xm[(i * 32 + rr) * 2]);
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const float mi = xm[(i * 32 + rr) * 2], li = xm[(i * 32 + rr) * 2 + 1];
+      if (mi == -INFINITY && li == 0.f) continue;   // a wave without keys
+      const float w = __builtin_amdgcn_exp2f(mi - M);
+      L = fmaf(w, li, L);
+      o += w * *(const f32x4*)(xo + (i * 32 + rr) * OP + c);
+    }
+    gstore((f32x4*)(O + row * D + h * DH + c), L > 0.f ? o / L : f32x4{0.f, 0.f, 0.f, 0.f});
+  }
+}
+
+// The other head widths: grid n_q, block 256; per head, online softmax over
+// 64-key tiles.
 __global__ __launch_bounds__(256) void k_attend_f32(const float* Q, const float* K, const float* V, int n_q,
                                                     int64_t n_kv, int H, int d_h, float qscale, float* O) {
   __shared__ float q[256];
@@ -198,6 +317,34 @@ hipError_t rs3_launch_attend_merge(const Rs3ReadoutArgs& a, int SA, float* O, hi
 hipError_t rs3_launch_attend_f32(const float* Q, const float* K, const float* V, int n_q, int64_t n_kv, int H,
                                  int d_h, float qscale, float* O, hipStream_t st) {
   if (n_q == 0) return hipSuccess;
+  // The general form takes the other head widths, no keys, and more heads than
+  // a grid's second dimension holds.
+  if (n_kv > 0 && H <= 65535 && (d_h == 32 || d_h == 64 || d_h == 128)) {
+    constexpr int NW = 8;
+    const dim3 grid((n_q + 31) / 32, H), blk(64 * NW);
+    const size_t lds = (size_t)NW * 32 * (d_h + 4 + 2) * 4;
+    if (d_h == 32)
+      hipLaunchKernelGGL((k_attend_f32_tile<32, NW>), grid, blk, lds, st, Q, K, V, n_q, n_kv, H, qscale, O);
+    else if (d_h == 64)
+      hipLaunchKernelGGL((k_attend_f32_tile<64, NW>), grid, blk, lds, st, Q, K, V, n_q, n_kv, H, qscale, O);
+    else
+      hipLaunchKernelGGL((k_attend_f32_tile<128, NW>), grid, blk, lds, st, Q, K, V, n_q, n_kv, H, qscale, O);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_attend_f32, dim3(n_q), dim3(256), 0, st, Q, K, V, n_q, n_kv, H, d_h, qscale, O);
   return hipGetLastError();
+}
+
+hipError_t rs3_attend_setup() {
+  const struct {
+    const void* f;
+    int d_h;
+  } ks[] = {{(const void*)k_attend_f32_tile<32, 8>, 32},
+            {(const void*)k_attend_f32_tile<64, 8>, 64},
+            {(const void*)k_attend_f32_tile<128, 8>, 128}};
+  for (const auto& k : ks) {
+    hipError_t e = hipFuncSetAttribute(k.f, hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 32 * (k.d_h + 6) * 4);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }

@@ -357,6 +357,7 @@ hipError_t rs3_launch_attend_prep(const AttendPrepArgs& p, hipStream_t st);
 hipError_t rs3_launch_attend_merge(const Rs3ReadoutArgs& a, int SA, float* O, hipStream_t st);
 hipError_t rs3_launch_attend_f32(const float* Q, const float* K, const float* V, int n_q, int64_t n_kv, int H,
                                  int d_h, float qscale, float* O, hipStream_t st);
+hipError_t rs3_attend_setup();
 // Projects the raw ring rows [hdr PSTART, + PLEN) of bank 0 of `a` into its
 // attention tiles (a.from_ring = 1), or, with rebuild = 1, rebuilds the
 // resident tile list and key count from the frame table.

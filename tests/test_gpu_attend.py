@@ -53,3 +53,30 @@ def test_attend_split_override_and_degenerate():
 def test_attend_f32_matches_oracle():
     got, exp, _ = _run(37, 150, 2, 32, "f32", seed=8)
     assert np.abs(got - exp).max() <= 1e-4
+
+
+@pytest.mark.parametrize("n_q,n_kv,H,d_h", [(1, 1, 1, 32), (32, 32, 1, 64), (33, 255, 2, 64), (65, 257, 3, 128),
+                                            (31, 600, 5, 32), (7, 70, 2, 40)])
+def test_attend_f32_query_tiles_and_key_groups(n_q, n_kv, H, d_h):
+    """Ragged last query tile and key group, waves without keys, every width of
+    the tiled form and one of the general form.  fp32 rounding of d_h- and
+    n_kv-long sums of values of order 1 stays below 600 * 2^-24 = 4e-5."""
+    got, exp, _ = _run(n_q, n_kv, H, d_h, "f32", seed=n_q * 7 + n_kv)
+    assert np.abs(got - exp).max() <= 4e-5
+
+
+def test_attend_f32_infinite_logits():
+    """Keys at logit -inf have weight 0, also where a wave sees no other."""
+    import paper_2608_22526_amd as rs3
+    n_q, n_kv, d_h = 5, 100, 32
+    rng = np.random.default_rng(3)
+    Q = np.ones((n_q, d_h), np.float32)
+    K = rng.standard_normal((n_kv, d_h)).astype(np.float32)
+    V = rng.standard_normal((n_kv, d_h)).astype(np.float32)
+    K[32:90, 0] = -np.inf
+    O = torch.full((n_q, d_h), float("nan"), device="cuda")
+    ws = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    rs3.attend(*(torch.from_numpy(a).cuda() for a in (Q, K, V)), n_q, n_kv, 1, d_h, rs3.RS3_F32, O, ws, 0)
+    keep = np.r_[0:32, 90:n_kv]
+    exp = oracle.attend(Q.astype(np.float64), K[keep].astype(np.float64), V[keep].astype(np.float64), H=1)
+    assert np.abs(O.cpu().numpy() - exp).max() <= 4e-5
