@@ -75,16 +75,16 @@ __device__ __forceinline__ void keep_s(const T& v) {
   asm volatile("" ::"s"(v));
 }
 
-// Work-group blk of c.blocks (256 threads) of a grid copy: each chunk is read
-// once and written to up to COPY_GROUP output grids (more of them go to further
-// work-groups: a small grid shared by many objects would otherwise be written by
-// a few CUs).  A thread has four chunks in flight; grids of fewer than 1,024 x
-// 256 chunks take one or a few per thread instead, so that every CU copies.
+// Work-group blk of c.blocks (256 threads) of a grid copy, a chunk per thread:
+// read once and written to up to COPY_GROUP output grids (more of them go to
+// further work-groups: a small grid shared by many objects would otherwise be
+// written by a few CUs).  Grids past 2,048 work-groups each loop.  64 grids of 8
+// MiB: 172 us; 2,048 work-groups in all with four chunks in flight per
+// thread took 216.
 constexpr int COPY_GROUP = 4;
-inline int copy_blocks(const Rs3CopyArgs& c, int64_t most) {
+inline int copy_blocks(const Rs3CopyArgs& c) {
   const int64_t groups = (c.copies + COPY_GROUP - 1) / COPY_GROUP, single = (c.n_x * c.count + 255) / 256;
-  const int64_t per = std::max<int64_t>((single + 3) / 4, std::min<int64_t>(single, 1024 / groups));
-  return (int)(std::min(per, std::max<int64_t>(1, most / groups)) * groups);
+  return (int)(std::min<int64_t>(single, 2048 * (int64_t)c.n_x) * groups);
 }
 
 __device__ __forceinline__ void copy_block(const Rs3CopyArgs& c, int blk) {
@@ -92,30 +92,11 @@ __device__ __forceinline__ void copy_block(const Rs3CopyArgs& c, int blk) {
   const int groups = (c.copies + COPY_GROUP - 1) / COPY_GROUP, cg = blk % groups;
   const int p0 = cg * COPY_GROUP, p1 = min(p0 + COPY_GROUP, c.copies);
   const int64_t step = (int64_t)(c.blocks / groups) * 256;
-  if (total <= step) {
-    const int64_t i = (int64_t)(blk / groups) * 256 + threadIdx.x;
-    if (i >= total) return;
-    const int64_t xi = c.n_x == 1 ? 0 : i / c.count;
+  for (int64_t i = (int64_t)(blk / groups) * 256 + threadIdx.x; i < total; i += step) {
+    const int64_t xi = c.n_x == 1 ? 0 : total >> 31 ? i / c.count : (uint32_t)i / (uint32_t)c.count;
     const u32x4 v = gload((const u32x4*)c.X + xi * c.x_stride + (i - xi * c.count));
     u32x4* y = (u32x4*)c.Y + xi * c.y_stride + (i - xi * c.count);
     for (int p = p0; p < p1; ++p) gstore(y + p * c.y_stride, v);
-    return;
-  }
-  for (int64_t i0 = (int64_t)(blk / groups) * 256 + threadIdx.x; i0 < total; i0 += 4 * step) {
-    u32x4 v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t i = i0 + k * step < total ? i0 + k * step : total - 1, xi = c.n_x == 1 ? 0 : i / c.count;
-      v[k] = gload((const u32x4*)c.X + xi * c.x_stride + (i - xi * c.count));
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t i = i0 + k * step;
-      if (i >= total) break;
-      const int64_t xi = c.n_x == 1 ? 0 : i / c.count;
-      u32x4* y = (u32x4*)c.Y + xi * c.y_stride + (i - xi * c.count);
-      for (int p = p0; p < p1; ++p) gstore(y + p * c.y_stride, v[k]);
-    }
   }
 }
 

@@ -1145,7 +1145,7 @@ hipError_t rs3_launch_readout(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, i
   const bool beside = a.max_sel > 0 && dtype == RS3_BF16 && !attn_projects(a);
   Rs3CopyArgs cp = rs3_grid_copy(a, dtype);
   if (a.copied) cp.Y = nullptr;
-  cp.blocks = cp.Y ? copy_blocks(cp, 2048) : 0;
+  cp.blocks = cp.Y ? copy_blocks(cp) : 0;
   if (cp.Y && !beside) {
     RS3_LAUNCH(RS3_K_COPY, st, k_copy_grid16, dim3(cp.blocks), dim3(256), 0, st, cp);
     hipError_t e = hipGetLastError();

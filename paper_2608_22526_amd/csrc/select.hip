@@ -1170,7 +1170,7 @@ hipError_t rs3_launch_energy_prior(const void* X, int64_t x_stride, int n_x, int
   // blocks beside the energies: one per group, or one per four mask rows
   const int n_more = a.row_box ? (a.n_obj * a.m + 3) / 4 : n_groups;
   Rs3CopyArgs cp = copy ? *copy : Rs3CopyArgs{};
-  cp.blocks = cp.Y && cp.copies > 1 ? copy_blocks(cp, 1024) : 0;
+  cp.blocks = cp.Y && cp.copies > 1 ? copy_blocks(cp) : 0;
   if (energy_wide(n_x, mn, qp)) {
     const int nbw = (mn + EW_ROWS - 1) / EW_ROWS, n_w = nbw * n_x;
     const dim3 gw(n_w + n_more + cp.blocks);
