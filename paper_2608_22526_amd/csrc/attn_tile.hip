@@ -88,9 +88,13 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
     return;
   }
   const bf16_t* qp = (const bf16_t*)a.Q + ((int64_t)o * a.max_sel + min(row, a.max_sel - 1)) * a.D + h * DH + 8 * g;
+  // rows past the count have no query in the workspace: theirs are 0, since
+  // what lies there must decide nothing for the rows beside them
   u32x4 q[NKS];
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks) q[ks] = gload((const u32x4*)(qp + 16 * ks));
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) q[ks] = row < cnt ? q[ks] : u32x4{0, 0, 0, 0};
   const TileEnt* tiles = ab.tiles[o];
   const bf16_t* Kh = (const bf16_t*)ab.kh[o] + (int64_t)h * KT * DH;
   const bf16_t* Vh = (const bf16_t*)ab.vh[o] + (int64_t)h * KT * DH;

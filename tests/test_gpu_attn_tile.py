@@ -2,10 +2,12 @@
 fp64: every head width, sizes at the edges of its tiles (32 queries, 64 keys, a
 window of 64 tiles per split), logits that outgrow the first tile's reference,
 and infinities."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
-from workloads import storage_to_f64, to_storage
+from workloads import make_weights, storage_to_f64, to_storage
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -82,3 +84,30 @@ def test_infinite_keys():
     got, ref = _attend(to_storage(Q, "bf16"), to_storage(K, "bf16"), _rand(rng, n_kv, 1, d_h), 1)
     assert np.isnan(ref[1::2]).all() and (got[1::2] == 0.0).all()
     assert np.abs(got[::2] - ref[::2]).max() <= 5e-2
+
+
+@pytest.mark.parametrize("H,rope", [(1, False), (2, False), (4, True), (8, True)])
+def test_result_does_not_depend_on_the_workspace(H, rope):
+    """Rows of the last query tile past the selected count are never written:
+    whatever the workspace holds there, the selected rows are the same bits."""
+    import paper_2608_22526_amd as rs3
+    from test_gpu_edge import SMALL, _dev, _host, _session
+    cfg = replace(SMALL, C=256, H=H, d_h=256 // H, d_kv=64, f_max=3, cap_frames=3)
+    sess = _session(cfg, make_weights(cfg, logit_scale=3.0), rope_theta=100.0 if rope else None)
+    rng = np.random.default_rng(H)
+    K, V, X = (_rand(rng, 1, cfg.mn, w) for w in (64, 64, 256))
+    full = _dev(np.ones((1, cfg.m, cfg.n), np.uint8))
+    for t in range(3):
+        sess.commit(_dev(np.roll(K, t, axis=1)), _dev(np.roll(V, t, axis=1)), full, t, t == 0)
+    Xd = _dev(X)
+    sess.select(full, Xd, [37])
+    n = rs3.readout_workspace_size(sess.layer, 1, cfg.mn)
+    out = []
+    for byte in (0, 0xFF, 0x7F, 0xFF):     # zeros, NaN, about 3e38
+        ws = torch.full((n,), byte, dtype=torch.uint8, device="cuda")
+        Y = torch.empty_like(Xd)
+        rs3.readout(sess.layer, sess.grid, 1, Xd, 0, sess.banks, sess.sel_idx, sess.sel_count, 0, cfg.mn, 0, Y, 0, ws=ws)
+        torch.cuda.synchronize()
+        out.append(_host(Y))
+    for y in out[1:]:
+        assert np.array_equal(y, out[0])
