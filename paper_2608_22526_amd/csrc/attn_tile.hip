@@ -9,12 +9,22 @@
 //
 // Softmax.  The logit product starts from -m (m the lane's reference) as its
 // accumulator input, so the exponentials need no subtraction.  m is the maximum
-// of the split's first tile and stays: a weight 2^x above it is exact (bf16
-// weights and fp32 sums have the same exponent range), so that the loop needs
-// no maximum, no test and no rescale per tile.  Only a logit more than about
-// 2^7 above the reference (in the exponent's base-2 units) can overflow; a
-// split whose sums come out too large or not finite is run again with the
-// reference kept at the running maximum.
+// of the split's first tile, and moves to a later tile's maximum when that tile
+// outweighs what came before it (SUM_RATIO below): its logits are still in
+// registers, and its weights are computed once more.  So the loop has no maximum
+// and no rescale per tile, only the test of a sum that it needs anyway.  The
+// move is for accuracy as much as for range.  A query's largest weight is then
+// exactly 1 or one of many, where against a fixed reference it is one more
+// rounded bf16 number.  Rounding error of the weights and partials, relative to
+// a reference at the maximum of half tiles that moves in steps of at least 2^8
+// (fp64 model, logits of deviation 2 to 6, 3,840 to 32,768 keys): fixed 1.02 to
+// 1.11, SUM_RATIO 0 and SUM_LOW 64 0.97 to 1.00, these 0.99 to 1.00.  On the
+// chip 4,096 queries against 28,672 keys, two heads of 128, are 0.004244 off
+// (fixed 0.004343, the half-tile form 0.004252).  A move costs about half a
+// tile, and the waves of a work-group wait for each other: that call took 126
+// us with the fixed reference and takes 137; five frames of a 128x128 grid with
+// eight heads of 32 1,606 and 1,807.
+// Whether a query's reference moves depends on that query alone.
 //
 // What bounds it: instruction issue.  Measured per SIMD (cycles at 2.4 GHz,
 // four waves): v_exp_f32 8.7, other VALU 5.6, a 32x32x16 MFMA 35; one wave
@@ -40,8 +50,9 @@
 
 namespace rs3 {
 
-// Largest row sum or output magnitude of a split that is taken as it is.
-constexpr float SUM_MAX = 0x1p120f;
+// The reference moves for a tile whose 32 weights in a lane sum to SUM_RATIO
+// times all before them, at least SUM_LOW and at most SUM_HIGH.
+constexpr float SUM_RATIO = 1.5f, SUM_LOW = 128.f, SUM_HIGH = 1024.f;
 
 template <int DH>
 struct TileLds {
@@ -152,127 +163,106 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
   for (int i = 0; i < 4; ++i) va[i] = L::VOFF + l31 * 128 + (((2 * i) ^ g ^ L::fv(l31)) << 4);
 
   f32x16 acc[NDT];
-  float m_run, l_run;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt) acc[dt] = f32x16{};
+  float m_run = 0.f, l_run = 0.f;
   constexpr bool BIAS = DH <= 128;   // -m kept as an accumulator input (16 registers)
   f32x16 nm = {};
-  // one pass over the split; safe: the reference follows the maximum
-  auto pass = [&](bool safe) {
 #pragma unroll
-    for (int j = 0; j < NST - 1; ++j)
-      if (j < nt) issue(j, j);
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) acc[dt] = f32x16{};
-    m_run = l_run = 0.f;
-    nm = f32x16{};
-    int slot = 0;
-    for (int j = 0; j < nt; ++j) {
-      wait_stages<2 * NL, NST - 2>(min(NST - 2, nt - 1 - j));   // stages that may still be in flight
-      stage_barrier();
-      const int idx = at(j) - cbase;
-      const uint32_t mk[2] = {(uint32_t)__builtin_amdgcn_readlane(c_mlo, idx),
-                              (uint32_t)__builtin_amdgcn_readlane(c_mhi, idx)};
-      if (j + NST - 1 < nt) {
-        if (at(j + NST - 1) - cbase >= 64) {   // (splits longer than the window) slide it to this tile
-          wait_vmcnt<0>();
-          cbase = at(j);
-          window();
-        }
-        issue(j + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+  for (int j = 0; j < NST - 1; ++j)
+    if (j < nt) issue(j, j);
+  int slot = 0;
+  for (int j = 0; j < nt; ++j) {
+    wait_stages<2 * NL, NST - 2>(min(NST - 2, nt - 1 - j));   // stages that may still be in flight
+    stage_barrier();
+    const int idx = at(j) - cbase;
+    const uint32_t mk[2] = {(uint32_t)__builtin_amdgcn_readlane(c_mlo, idx),
+                            (uint32_t)__builtin_amdgcn_readlane(c_mhi, idx)};
+    if (j + NST - 1 < nt) {
+      if (at(j + NST - 1) - cbase >= 64) {   // (splits longer than the window) slide it to this tile
+        wait_vmcnt<0>();
+        cbase = at(j);
+        window();
       }
-      const uint8_t* st = lds + slot * L::STAGE;
-      slot = slot == NST - 1 ? 0 : slot + 1;
-      // logits of both halves, less the reference; -inf where not resident
-      f32x16 sc[2];
+      issue(j + NST - 1, slot == 0 ? NST - 1 : slot - 1);
+    }
+    const uint8_t* st = lds + slot * L::STAGE;
+    slot = slot == NST - 1 ? 0 : slot + 1;
+    // logits of both halves, less the reference; -inf where not resident
+    f32x16 sc[2];
 #pragma unroll
-      for (int kh = 0; kh < 2; ++kh) {
-        constexpr int KB = NKS < 4 ? NKS : 4;
+    for (int kh = 0; kh < 2; ++kh) {
+      constexpr int KB = NKS < 4 ? NKS : 4;
 #pragma unroll
-        for (int k0 = 0; k0 < NKS; k0 += KB) {
-          u32x4 kf[KB];
+      for (int k0 = 0; k0 < NKS; k0 += KB) {
+        u32x4 kf[KB];
 #pragma unroll
-          for (int i = 0; i < KB; ++i) kf[i] = *(const u32x4*)(st + ka[k0 + i] + kh * 32 * DH * 2);
+        for (int i = 0; i < KB; ++i) kf[i] = *(const u32x4*)(st + ka[k0 + i] + kh * 32 * DH * 2);
 #pragma unroll
-          for (int i = 0; i < KB; ++i) {
-            if (k0 + i == 0)
-              sc[kh] = mfma32(kf[i], q[0], BIAS ? nm : f32x16{});
-            else
-              sc[kh] = mfma32(kf[i], q[k0 + i], sc[kh]);
-          }
-        }
-        if (mk[kh] != 0xffffffffu) {   // frame boundary
-          const uint32_t m = mk[kh] >> (4 * g);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sc[kh][r] = m >> (8 * (r >> 2) + (r & 3)) & 1u ? sc[kh][r] : -INFINITY;
+        for (int i = 0; i < KB; ++i) {
+          if (k0 + i == 0)
+            sc[kh] = mfma32(kf[i], q[0], BIAS ? nm : f32x16{});
+          else
+            sc[kh] = mfma32(kf[i], q[k0 + i], sc[kh]);
         }
       }
-      float sub = BIAS ? 0.f : m_run;
-      if (j == 0 || safe) {
-        float mx = sc[0][0];
+      if (mk[kh] != 0xffffffffu) {   // frame boundary
+        const uint32_t m = mk[kh] >> (4 * g);
 #pragma unroll
-        for (int r = 1; r < 16; ++r) mx = max3f(mx, sc[0][r], sc[1][r]);
-        mx = max_with_partner(__builtin_elementwise_maximum(mx, sc[1][0])) - sub;
-        // the reference moves to the tile's maximum where that grew (always
-        // on the first tile, whose accumulators are still 0)
-        const float d = j == 0 || mx > 0.f ? mx : 0.f;
-        const float alpha = j == 0 ? 1.f : __builtin_amdgcn_exp2f(-d);
-        l_run *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
-        m_run += d;
-        nm -= d;
-        sub = BIAS ? d : m_run;
+        for (int r = 0; r < 16; ++r) sc[kh][r] = m >> (8 * (r >> 2) + (r & 3)) & 1u ? sc[kh][r] : -INFINITY;
       }
-      // weights, their row sums, and O^T += V^T P^T (four 16-key steps)
-      u32x4 pk[4];
+    }
+    // weights against the reference, and their sum over this lane's keys
+    u32x4 pk[4];
+    float ts = 0.f;
+    auto weights = [&](float sub) {
+      float t[2] = {0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float x0 = sc[i >> 1][8 * (i & 1) + 2 * e], x1 = sc[i >> 1][8 * (i & 1) + 2 * e + 1];
           pk[i][e] = pack_bf16x2(__builtin_amdgcn_exp2f(x0 - sub), __builtin_amdgcn_exp2f(x1 - sub));
-          l_run = add_bf16x2(pk[i][e], l_run);
+          t[i >> 1] = add_bf16x2(pk[i][e], t[i >> 1]);
         }
+      ts = t[0] + t[1];
+    };
+    if (j > 0) weights(BIAS ? 0.f : m_run);
+    const bool hit = !(ts < __builtin_amdgcn_fmed3f(SUM_RATIO * l_run, SUM_LOW, SUM_HIGH));   // also for NaN
+    if (j == 0 || __any(hit)) {
+      // the reference of the queries whose sum asks for it moves to the tile's
+      // maximum (on the first tile: of all, whose accumulators are still 0);
+      // the weights of the others come out the same again
+      float mx = sc[0][0];
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) {
-        u32x4 vf[4];
+      for (int r = 1; r < 16; ++r) mx = max3f(mx, sc[0][r], sc[1][r]);
+      mx = max_with_partner(__builtin_elementwise_maximum(mx, sc[1][0])) - (BIAS ? 0.f : m_run);
+      const float d = j == 0 || max_with_partner(hit ? 1.f : 0.f) > 0.f ? mx : 0.f;
+      const float alpha = j == 0 ? 1.f : __builtin_amdgcn_exp2f(-d);
+      l_run *= alpha;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) vf[i] = *(const u32x4*)(st + va[i] + dt * 32 * 128);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[dt] = mfma32(vf[i], pk[i], acc[dt]);
-      }
+      for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
+      m_run += d;
+      nm -= d;
+      weights(BIAS ? d : m_run);
     }
-  };
-  // The row sum over both lane groups, and whether every wave's results are in
-  // range (the stages are free after the first barrier).
-  auto finish = [&]() {
-    l_run = sum_with_partner(l_run);
-    float big = l_run;
+    l_run += ts;
+    // O^T += V^T P^T (four 16-key steps)
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
+    for (int dt = 0; dt < NDT; ++dt) {
+      u32x4 vf[4];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) big = __builtin_elementwise_maximum(big, __builtin_fabsf(acc[dt][r]));
-    int* flags = (int*)(lds + NST * L::STAGE - 64);
-    __syncthreads();
-    if (lane == 0) flags[wave] = 1;
-    if (!(big <= SUM_MAX)) flags[wave] = 0;   // also for NaN
-    __syncthreads();
-    int all = 1;
+      for (int i = 0; i < 4; ++i) vf[i] = *(const u32x4*)(st + va[i] + dt * 32 * 128);
 #pragma unroll
-    for (int w = 0; w < NW; ++w) all &= flags[w];
-    return all != 0;
-  };
-  pass(false);
-  if (!finish()) {
-    __syncthreads();   // every wave has read the flags
-    cbase = tb;
-    window();
-    pass(true);
-    finish();
+      for (int i = 0; i < 4; ++i) acc[dt] = mfma32(vf[i], pk[i], acc[dt]);
+    }
   }
+  l_run = sum_with_partner(l_run);
+  __syncthreads();   // the stages are free
   // Epilogue: this wave's normalised rows through LDS as [query][d] bf16,
   // then whole rows in 16-byte stores.
   constexpr int OP = DH * 2 + 16;
-  static_assert(NW * 32 * OP <= NST * L::STAGE - 64, "the rows fit the stages beside the flags");
+  static_assert(NW * 32 * OP <= NST * L::STAGE, "the rows fit the stages");
   uint8_t* ow = lds + wave * 32 * OP;
   const float inv = l_run > 0.f ? __builtin_amdgcn_rcpf(l_run) : 0.f;
 #pragma unroll
@@ -285,21 +275,13 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
       *(u32x2*)(ow + l31 * OP + (32 * dt + 8 * q4 + 4 * g) * 2) = w;
     }
   if (g == 0 && row < cnt) {
-    // a sum far above its reference hands the merge its exponent with the
-    // reference: e^(m - M) of the merge must not vanish while l is large
-    float mo = m_run, lo = l_run;
-    if (lo > 0x1p32f) {
-      const int e = __builtin_amdgcn_frexp_expf(lo);
-      mo += (float)e;
-      lo = __builtin_amdgcn_ldexpf(lo, -e);
-    }
     float* p = ml + (int64_t)row * H * 2;
     if (a.stream_parts) {
-      pstore(p, mo);
-      pstore(p + 1, lo);
+      pstore(p, m_run);
+      pstore(p + 1, l_run);
     } else {
-      p[0] = mo;
-      p[1] = lo;
+      p[0] = m_run;
+      p[1] = l_run;
     }
   }
   // the staged rows of a wave are written and read by that wave alone

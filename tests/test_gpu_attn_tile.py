@@ -111,3 +111,32 @@ def test_result_does_not_depend_on_the_workspace(H, rope):
         out.append(_host(Y))
     for y in out[1:]:
         assert np.array_equal(y, out[0])
+
+
+@pytest.mark.parametrize("d_h", [32, 64, 128, 256])
+def test_largest_weight_is_exact(d_h):
+    """Two keys far above the first tile share a query: the larger one's weight
+    is exactly 1, so the error is that of the smaller one's weight and of the
+    result in bf16.  Both weights kept against the first tile's maximum, as
+    rounded numbers, are 1.2 times as far off."""
+    n_q, n_kv = 3000, 64 * 5
+    rng = np.random.default_rng(d_h)
+    a = rng.uniform(11.0, 14.0, n_q)
+    Q = np.zeros((n_q, 1, d_h), np.float32)
+    Q[:, 0, 0] = a * np.sqrt(d_h) / 1.4426950408889634
+    Q[:, 0, 1] = (a - rng.uniform(0.1, 1.0, n_q)) * np.sqrt(d_h) / 1.4426950408889634
+    K = np.zeros((n_kv, 1, d_h), np.float32)
+    K[130, 0, 0] = K[200, 0, 1] = 1.0
+    V = np.zeros((n_kv, 1, d_h), np.float32)
+    V[130], V[200] = 1.0, -1.0
+    q = to_storage(Q, "bf16")
+    got, _ = _attend(q, to_storage(K, "bf16"), to_storage(V, "bf16"), 1)
+    bf = lambda x: storage_to_f64(to_storage(np.asarray(x, np.float32), "bf16"), "bf16")
+    # base-2 logits as the kernel has them (queries scaled in fp32, rounded once)
+    s = bf(storage_to_f64(q, "bf16").astype(np.float32)[:, 0, :2] * np.float32(1.4426950408889634 / np.sqrt(d_h)))
+    rest = (n_kv - 2) * np.exp2(-s[:, 0])
+    w = np.exp2(s[:, 1] - s[:, 0])
+    exact = (1.0 - w) / (1.0 + w + rest)
+    rounded = bf((1.0 - bf(w)) / (1.0 + bf(w) + rest))
+    rms = lambda e: np.sqrt(np.mean(e * e))
+    assert rms(got[:, 0, 0] - exact) <= 1.1 * rms(rounded - exact)
