@@ -166,6 +166,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt) acc[dt] = f32x16{};
   float m_run = 0.f, l_run = 0.f;
+  bool unseen = true;   // no finite logit so far: the reference is still to be set
   constexpr bool BIAS = DH <= 128;   // -m kept as an accumulator input (16 registers)
   f32x16 nm = {};
 #pragma unroll
@@ -228,17 +229,20 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
       ts = t[0] + t[1];
     };
     if (j > 0) weights(BIAS ? 0.f : m_run);
-    const bool hit = !(ts < __builtin_amdgcn_fmed3f(SUM_RATIO * l_run, SUM_LOW, SUM_HIGH));   // also for NaN
-    if (j == 0 || __any(hit)) {
+    const bool hit = unseen || !(ts < __builtin_amdgcn_fmed3f(SUM_RATIO * l_run, SUM_LOW, SUM_HIGH));   // also for NaN
+    if (__any(hit)) {
       // the reference of the queries whose sum asks for it moves to the tile's
-      // maximum (on the first tile: of all, whose accumulators are still 0);
+      // maximum, and so does that of the unseen ones (all of them on the first
+      // tile), whose accumulators are 0, if the tile has a logit above -inf;
       // the weights of the others come out the same again
       float mx = sc[0][0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) mx = max3f(mx, sc[0][r], sc[1][r]);
       mx = max_with_partner(__builtin_elementwise_maximum(mx, sc[1][0])) - (BIAS ? 0.f : m_run);
-      const float d = j == 0 || max_with_partner(hit ? 1.f : 0.f) > 0.f ? mx : 0.f;
-      const float alpha = j == 0 ? 1.f : __builtin_amdgcn_exp2f(-d);
+      const bool move = max_with_partner(hit ? 1.f : 0.f) > 0.f && !(unseen && mx == -INFINITY);
+      const float d = move ? mx : 0.f;
+      const float alpha = unseen ? 1.f : __builtin_amdgcn_exp2f(-d);
+      unseen = unseen && !move;
       l_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) acc[dt] *= alpha;
@@ -276,11 +280,12 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
     }
   if (g == 0 && row < cnt) {
     float* p = ml + (int64_t)row * H * 2;
+    const float m = unseen ? -INFINITY : m_run;
     if (a.stream_parts) {
-      pstore(p, m_run);
+      pstore(p, m);
       pstore(p + 1, l_run);
     } else {
-      p[0] = m_run;
+      p[0] = m;
       p[1] = l_run;
     }
   }

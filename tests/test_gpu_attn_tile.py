@@ -140,3 +140,24 @@ def test_largest_weight_is_exact(d_h):
     rounded = bf((1.0 - bf(w)) / (1.0 + bf(w) + rest))
     rms = lambda e: np.sqrt(np.mean(e * e))
     assert rms(got[:, 0, 0] - exact) <= 1.1 * rms(rounded - exact)
+
+
+@pytest.mark.parametrize("d_h", [32, 64, 128, 256])
+def test_first_tile_at_minus_infinity(d_h):
+    """Products that overflow to -inf over the whole first tile (and, for some
+    queries, the first two), beside queries for which they do not: every query
+    reads the keys that it has."""
+    rng = np.random.default_rng(d_h)
+    n_q, n_kv = 70, 64 * 6 + 10
+    Q, K = rng.standard_normal((n_q, 1, d_h)).astype(np.float32), rng.standard_normal((n_kv, 1, d_h)).astype(np.float32)
+    K[:, 0, :3] = 0.0
+    K[:64, 0, 0] = K[64:128, 0, 1] = -3e38
+    K[128:, 0, 2] = -1.0
+    Q[:, 0, :3] = 0.0
+    Q[::2, 0, 0] = 1e3                     # -inf on the first tile
+    Q[::4, 0, 1] = 1e3                     # and on the second
+    Q[::8, 0, 2] = 300.0 * np.sqrt(d_h)    # the keys left are far below 0
+    V = _rand(rng, n_kv, 1, d_h)
+    for n_splits in (1, 2, 4):   # four: the first split holds the first two tiles alone
+        got, ref = _attend(to_storage(Q, "bf16"), to_storage(K, "bf16"), V, n_splits)
+        assert np.abs(got - ref).max() <= 5e-2
