@@ -161,6 +161,10 @@ rs3_status rs3_layer_set_rope_axial(rs3_layer* L, int32_t m, int32_t n, double t
  * kept cell index (`pos`) per row, and the rows projected by W_k / W_v of
  * the layer it was created for (whose memory stays until its last bank is
  * destroyed, also when rs3_layer_destroy comes first).
+ * Rows that are not finite (Inf, NaN): an evicted frame's may still reach a
+ * readout where the ring keeps them in one half of a 64-key tile with resident
+ * rows (fp32 layers without a workspace: in one tile), until they are
+ * overwritten; anywhere else they take no part.
  * Requires 0 <= n_pin < f_max <= 256, 1 <= cap <= 2^26. */
 rs3_status rs3_bank_create(const rs3_layer* L, int32_t cap, int32_t f_max,
                            int32_t n_pin, rs3_bank** out);

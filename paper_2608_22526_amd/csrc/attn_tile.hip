@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
       }
       issue(j + NST - 1, slot == 0 ? NST - 1 : slot - 1);
     }
-    const uint8_t* st = lds + slot * L::STAGE;
+    uint8_t* st = lds + slot * L::STAGE;
     slot = slot == NST - 1 ? 0 : slot + 1;
     // logits of both halves, less the reference; -inf where not resident
     f32x16 sc[2];
@@ -211,6 +211,14 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
         const uint32_t m = mk[kh] >> (4 * g);
 #pragma unroll
         for (int r = 0; r < 16; ++r) sc[kh][r] = m >> (8 * (r >> 2) + (r & 3)) & 1u ? sc[kh][r] : -INFINITY;
+        // a half without resident rows may hold values that are no numbers,
+        // which a weight of 0 does not hide: each wave clears its V^ for itself
+        // (all write the same; a branch in the product took 9 % of its time)
+        if (mk[kh] == 0u)
+          for (int i = lane; i < DH * 4; i += 64) {
+            const int d = i >> 2, c = 4 * kh + (i & 3);
+            *(u32x4*)(st + L::VOFF + d * 128 + ((c ^ L::fv(d)) << 4)) = u32x4{0, 0, 0, 0};
+          }
       }
     }
     // weights against the reference, and their sum over this lane's keys

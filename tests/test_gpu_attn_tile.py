@@ -161,3 +161,37 @@ def test_first_tile_at_minus_infinity(d_h):
     for n_splits in (1, 2, 4):   # four: the first split holds the first two tiles alone
         got, ref = _attend(to_storage(Q, "bf16"), to_storage(K, "bf16"), V, n_splits)
         assert np.abs(got - ref).max() <= 5e-2
+
+
+@pytest.mark.parametrize("H", [1, 2, 4, 8])
+@pytest.mark.parametrize("kept", [20, 32, 84])
+def test_dead_half_of_a_tile(H, kept):
+    """Rows of an evicted frame that are not finite, in the half of a tile that
+    no resident row shares: they take no part."""
+    from harness import TOL, OraclePipeline
+    from test_gpu_edge import SMALL, _dev, _host, _session
+    import oracle
+    cfg = replace(SMALL, C=256, H=H, d_h=256 // H, d_kv=64, f_max=2, n_pin=1, cap_frames=1)
+    W = make_weights(cfg)
+    sess, orc = _session(cfg, W, rope_theta=100.0), OraclePipeline(cfg, W)
+    orc.rope = oracle.axial_table(cfg.m, cfg.n, cfg.d_h, 100.0)
+    rng = np.random.default_rng(kept + H)
+    for t, n in enumerate((0, 470, kept)):     # the third wraps to the start and evicts the second
+        K, V = (rng.standard_normal((1, cfg.mn, cfg.d_kv)).astype(np.float32) for _ in range(2))
+        if n == 470:
+            V[0, (kept + 31) // 32 * 32:] = np.inf
+            V[0, 200:300] = np.nan
+        mask = np.zeros((1, cfg.mn), np.uint8)
+        mask[0, :n] = 1
+        mask = mask.reshape(1, cfg.m, cfg.n)
+        K, V = to_storage(K, "bf16"), to_storage(V, "bf16")
+        sess.commit(_dev(K), _dev(V), _dev(mask), t, t == 0)
+        orc.commit(K, V, mask, t, t == 0)
+    X = _rand(rng, 1, cfg.mn, cfg.C)
+    Xd, full = _dev(X), np.ones((1, cfg.m, cfg.n), np.uint8)
+    sess.select(_dev(full), Xd, [50])
+    rows = orc.select(full, X, [50])[0][0]
+    Y = torch.zeros((1, cfg.mn, cfg.C), dtype=torch.bfloat16, device="cuda")
+    sess.readout(Xd, Y)
+    got = storage_to_f64(_host(Y)[0][rows], "bf16")
+    assert np.abs(got - orc.readout_rows(X, 0, rows)).max() <= TOL["bf16"]
