@@ -191,7 +191,8 @@ __global__ __launch_bounds__(64 * NW) void k_attend_f32_tile(const float* Q, con
     mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     if (__any(mx > m_run)) {
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first group
+      // 0 on a lane's first logits; while it has none, there is nothing to scale
+      const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < DH / 32; ++dt) acc[dt] *= alpha;

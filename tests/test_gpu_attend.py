@@ -80,3 +80,21 @@ def test_attend_f32_infinite_logits():
     keep = np.r_[0:32, 90:n_kv]
     exp = oracle.attend(Q.astype(np.float64), K[keep].astype(np.float64), V[keep].astype(np.float64), H=1)
     assert np.abs(O.cpu().numpy() - exp).max() <= 4e-5
+
+
+def test_attend_f32_infinite_logits_of_some_queries():
+    """Products that overflow to -inf over a wave's whole first key group for
+    some queries and not for others: every query reads the keys that it has."""
+    import paper_2608_22526_amd as rs3
+    n_q, n_kv, d_h = 40, 300, 32
+    rng = np.random.default_rng(4)
+    Q, K, V = (rng.standard_normal((n, d_h)).astype(np.float32) for n in (n_q, n_kv, n_kv))
+    K[:, 0] = 0.0
+    K[:32, 0] = K[64:96, 0] = -3e38
+    Q[:, 0] = 0.0
+    Q[::3, 0] = 100.0
+    O = torch.full((n_q, d_h), 7.0, device="cuda")
+    ws = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    rs3.attend(*(torch.from_numpy(a).cuda() for a in (Q, K, V)), n_q, n_kv, 1, d_h, rs3.RS3_F32, O, ws, 0)
+    exp = oracle.attend(Q.astype(np.float64), K.astype(np.float64), V.astype(np.float64), H=1)
+    assert np.abs(O.cpu().numpy() - exp).max() <= 4e-5
