@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_attend_merge(Rs3ReadoutArgs a, int SA, 
 // four heads of 128: 5,727 and 111 us (77 TFLOP/s); 4 x 7,000, one head of 64:
 // 1,478 and 158 us.
 template <int DH, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attend_f32_tile(const float* Q, const float* K, const float* V, int n_q,
+__global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : 2) void k_attend_f32_tile(const float* Q, const float* K, const float* V, int n_q,
                                                              int64_t n_kv, int H, float qscale, float* O) {
   constexpr int OP = DH + 4;
   extern __shared__ __attribute__((aligned(16))) float xo[];   // [NW][32][OP], then (m, l) [NW][32][2]
@@ -214,6 +214,11 @@ __global__ __launch_bounds__(64 * NW) void k_attend_f32_tile(const float* Q, con
       for (int r = 0; r < 16; ++r) {
         const int64_t j = j0 + c_row(r, lane);
         v[r] = gload(vp + (j < n_kv ? j : n_kv - 1) * D + 32 * dt);
+      }
+      if (n_kv - j0 < 32) {   // a repeated key adds 0 whatever its value is
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (c_row(r, lane) >= (int)(n_kv - j0)) v[r] = 0.f;
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[r], sc[r], acc[dt], 0, 0, 0);

@@ -98,3 +98,23 @@ def test_attend_f32_infinite_logits_of_some_queries():
     rs3.attend(*(torch.from_numpy(a).cuda() for a in (Q, K, V)), n_q, n_kv, 1, d_h, rs3.RS3_F32, O, ws, 0)
     exp = oracle.attend(Q.astype(np.float64), K.astype(np.float64), V.astype(np.float64), H=1)
     assert np.abs(O.cpu().numpy() - exp).max() <= 4e-5
+
+
+@pytest.mark.parametrize("n_kv", [1, 33, 290])
+def test_attend_f32_infinite_last_value(n_kv):
+    """The short last key group repeats its last key with weight 0: an infinite
+    value there is read once."""
+    import paper_2608_22526_amd as rs3
+    n_q, d_h = 33, 64
+    rng = np.random.default_rng(n_kv)
+    Q, K, V = (rng.standard_normal((n, d_h)).astype(np.float32) for n in (n_q, n_kv, n_kv))
+    V[-1, 5], V[-1, 40] = np.inf, -np.inf
+    O = torch.full((n_q, d_h), 7.0, device="cuda")
+    ws = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    rs3.attend(*(torch.from_numpy(a).cuda() for a in (Q, K, V)), n_q, n_kv, 1, d_h, rs3.RS3_F32, O, ws, 0)
+    got = O.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        exp = oracle.attend(Q.astype(np.float64), K.astype(np.float64), V.astype(np.float64), H=1)
+    assert (got[:, 5] == np.inf).all() and (got[:, 40] == -np.inf).all()
+    rest = np.setdiff1d(np.arange(d_h), [5, 40])
+    assert np.abs(got[:, rest] - exp[:, rest]).max() <= 4e-5
