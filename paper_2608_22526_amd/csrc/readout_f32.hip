@@ -150,19 +150,22 @@ __global__ __launch_bounds__(RF_THREADS) void k_attn_f32(Rs3ReadoutArgs a, int G
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));   // finite: the half tile has a resident key
+    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     if (__any(mx > m_run)) {
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first half tile
+      // 0 on a lane's first logits; while all of them are -inf (products that
+      // overflow), there is nothing to scale
+      const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < DH / 32; ++dt) acc[dt] *= alpha;
       m_run = m_new;
     }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;   // every logit so far -inf: weights 0
     float ls4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      sc[r] = __builtin_amdgcn_exp2f(sc[r] - m_run);
+      sc[r] = __builtin_amdgcn_exp2f(sc[r] - m_use);
       ls4[r & 3] += sc[r];
     }
     l_run += (ls4[0] + ls4[1]) + (ls4[2] + ls4[3]);

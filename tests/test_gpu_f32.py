@@ -113,3 +113,43 @@ def test_tiled_readout_and_commit(H, d_h, d_kv, n_obj, absorb, rope, k, kept):
         ys.append((_host(Y), _host(Y2), s2.banks[0].export()["K"]))
     for a, b in zip(*ys):
         assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+
+
+@pytest.mark.parametrize("H,all_keys", [(1, False), (2, False), (1, True)])
+def test_overflowing_logits(H, all_keys):
+    """Logits that overflow to -inf over the first half tile, or over every key
+    of head 0: a query reads the keys that it has, and the other heads whatever
+    head 0 holds.  The workspace form and the direct form agree."""
+    import paper_2608_22526_amd as rs3
+    from types import SimpleNamespace
+    d_h = 64 // H
+    cfg = replace(CONFIGS["tiny_f32"], C=64, H=H, d_h=d_h, d_kv=64, f_max=3, n_pin=1, cap_frames=2)
+    eye = np.eye(64, dtype=np.float32)
+    sess = _session(cfg, SimpleNamespace(Wq=eye, Wk=eye, Wv=eye, Wo=eye))
+    rng = np.random.default_rng(H)
+    K, V, X = (rng.standard_normal((1, cfg.mn, 64)).astype(np.float32) for _ in range(3))
+    K[..., 0] = 0.0
+    K[0, :cfg.mn if all_keys else 40, 0] = -3e38
+    X[..., 0] = 0.0
+    X[0, ::3, 0] = 100.0
+    sess.commit(_dev(K), _dev(V), _dev(_first(cfg, 100)[None]), 0, True)
+    Xd, full = _dev(X), _dev(np.ones((1, cfg.m, cfg.n), np.uint8))
+    sess.select(full, Xd, [cfg.mn])
+    ys = []
+    for ws in (sess.ws_read, None):
+        Y = torch.zeros((1, cfg.mn, 64), device="cuda")
+        rs3.readout(sess.layer, sess.grid, 1, Xd, 0, sess.banks, sess.sel_idx, sess.sel_count, 0, cfg.mn, 0, Y, 0, ws=ws)
+        torch.cuda.synchronize()
+        ys.append(_host(Y)[0])
+    rows = np.arange(cfg.mn)
+    exp = X[0].astype(np.float64)
+    for h in range(H):
+        c = slice(h * d_h, (h + 1) * d_h)
+        s = X[0, rows, c].astype(np.float64) @ K[0, :100, c].astype(np.float64).T / np.sqrt(d_h)
+        s[s < -3e38] = -np.inf
+        m = s.max(axis=1, keepdims=True)
+        p = np.exp(s - np.where(np.isfinite(m), m, 0.0))
+        l = p.sum(axis=1, keepdims=True)
+        exp[rows, c] += np.where(l > 0, p / np.where(l > 0, l, 1.0), 0.0) @ V[0, :100, c].astype(np.float64)
+    for y in ys:
+        assert np.abs(y - exp).max() <= TOL
