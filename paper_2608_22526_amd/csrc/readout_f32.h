@@ -54,7 +54,7 @@ __device__ __forceinline__ void merge_f32_block(const Rs3ReadoutArgs& a, int o, 
   const int r0 = ry * RF_ROWS, S = a.S, H = a.H, D = a.D, C = a.C, OP = D + 4;
   float* os = dyn;
   float* wl = os + 32 * OP;        // [h][s][row]
-  float* live = wl + 32 * H * S;   // [row]: 1 if the row saw a resident key
+  float* live = wl + 32 * H * S;   // [row]: 1 if a head of the row has weight on a key
   const int32_t* sel = a.sel_idx + (int64_t)o * a.sel_stride;
   int cnt = gload(a.sel_count + (a.sel_stride ? o : 0));
   // the rows this thread stores: rt + r, r < 4
@@ -71,6 +71,8 @@ __device__ __forceinline__ void merge_f32_block(const Rs3ReadoutArgs& a, int o, 
     cnt = cnt < 0 ? 0 : a.max_sel;
   }
   if (r0 >= cnt) return;
+  if (tid < 32) live[tid] = 0.f;
+  lds_barrier();
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     if (r0 + rt + r >= cnt)
@@ -96,7 +98,7 @@ __device__ __forceinline__ void merge_f32_block(const Rs3ReadoutArgs& a, int o, 
     }
     const float inv = den > 0.f ? 1.f / den : 0.f;
     for (int s = 0; s < S; ++s) wl[(h * S + s) * 32 + row] *= inv;
-    if (h == 0) live[row] = den > 0.f ? 1.f : 0.f;
+    if (den > 0.f) live[row] = 1.f;   // from any head: one may have no finite logit
   }
   lds_barrier();
   const int lg_dh = 31 - __clz(a.d_h), cpr = D / 4;

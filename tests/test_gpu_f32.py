@@ -115,7 +115,7 @@ def test_tiled_readout_and_commit(H, d_h, d_kv, n_obj, absorb, rope, k, kept):
         assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
 
 
-@pytest.mark.parametrize("H,all_keys", [(1, False), (2, False), (1, True)])
+@pytest.mark.parametrize("H,all_keys", [(1, False), (2, False), (1, True), (2, True)])
 def test_overflowing_logits(H, all_keys):
     """Logits that overflow to -inf over the first half tile, or over every key
     of head 0: a query reads the keys that it has, and the other heads whatever
