@@ -160,7 +160,8 @@ rs3_status rs3_layer_set_rope_axial(rs3_layer* L, int32_t m, int32_t n, double t
  * Zero-length frames are recorded.  The bank stores the raw K/V rows, the
  * kept cell index (`pos`) per row, and the rows projected by W_k / W_v of
  * the layer it was created for (whose memory stays until its last bank is
- * destroyed, also when rs3_layer_destroy comes first).
+ * destroyed, also when rs3_layer_destroy comes first; a layer and its banks may
+ * be destroyed from several host threads).
  * Rows that are not finite (Inf, NaN): an evicted frame's may still reach a
  * readout where the ring keeps them in one half of a 64-key tile with resident
  * rows (fp32 layers without a workspace: in one tile), until they are
@@ -231,7 +232,7 @@ rs3_status rs3_select_queries(const rs3_grid* g, int32_t n_obj, const uint8_t* m
  *          for per-object lists or 0 for one shared list
  * max_sel: upper bound on every sel_count used (host grid size), <= m*n
  * n_splits: key splits per query tile (0 = automatic); n_splits*H <= 256 (fp32
- *          layers take at most 128/H of them)
+ *          layers take at most 64 and at most 128/H of them)
  * Y      : [n_obj][m*n][C] with stride y_obj_stride (elements); may equal X
  *          (in place) only when n_obj == 1 or X is per object with the same
  *          stride.  y_fp32 = 1 writes Y as fp32 for diagnostics (never in

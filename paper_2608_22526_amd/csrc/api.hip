@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -20,8 +21,10 @@ struct rs3_track {
 
 struct rs3_layer {
   LayerDev dev;         // host copy holding device pointers
-  mutable int n_banks;  // banks created from the layer and not yet destroyed
-  bool destroyed;       // destroyed by the caller while banks were alive: freed with the last of them
+  // The caller's handle and each of the layer's banks hold one; whoever gives
+  // back the last frees the layer (from any host thread).
+  mutable std::atomic<int> refs{1};
+  bool has_banks() const { return refs.load() > 1; }
 };
 
 struct rs3_bank {
@@ -289,8 +292,9 @@ rs3_status rs3_layer_create(int32_t C, int32_t H, int32_t d_kv, rs3_dtype dt, in
   return RS3_OK;
 }
 
-// Frees a layer that no bank refers to.
-static void layer_free(const rs3_layer* L) {
+// Gives back one reference to the layer, and the layer with the last.
+static void layer_release(const rs3_layer* L) {
+  if (L->refs.fetch_sub(1) > 1) return;
   void* w[5] = {L->dev.WqT, L->dev.WkT, L->dev.WvT, L->dev.WoT, L->dev.rope};
   for (void* p : w)
     if (p) (void)hipFree(p);
@@ -298,20 +302,16 @@ static void layer_free(const rs3_layer* L) {
 }
 
 void rs3_layer_destroy(rs3_layer* L) {
-  if (!L) return;
-  // A bank counts itself out of its layer when it is destroyed.  A garbage
-  // collector may finalise the layer first, so the layer then waits for it.
-  if (L->n_banks > 0)
-    L->destroyed = true;
-  else
-    layer_free(L);
+  // A garbage collector may finalise the layer before its banks: its memory
+  // then stays until the last of them is destroyed.
+  if (L) layer_release(L);
 }
 
 // ---- rotary table ------------------------------------------------------------
 namespace {
 
 rs3_status rope_args_ok(const rs3_layer* L, int32_t m, int32_t n) {
-  if (!L || L->dev.absorb || L->n_banks > 0 || L->dev.dah % 2 != 0) return RS3_E_INVALID;
+  if (!L || L->dev.absorb || L->has_banks() || L->dev.dah % 2 != 0) return RS3_E_INVALID;
   if (m <= 0 || n <= 0 || (int64_t)m * n > RS3_MAX_MN) return RS3_E_INVALID;
   return RS3_OK;
 }
@@ -338,7 +338,7 @@ void rope_install(rs3_layer* L, float* t, int32_t m, int32_t n) {
 rs3_status rs3_layer_set_rope(rs3_layer* L, int32_t m, int32_t n, const float* table) {
   if (!L) return RS3_E_INVALID;
   if (!table) {
-    if (m != 0 || n != 0 || L->dev.absorb || L->n_banks > 0) return RS3_E_INVALID;
+    if (m != 0 || n != 0 || L->dev.absorb || L->has_banks()) return RS3_E_INVALID;
     rope_install(L, nullptr, 0, 0);
     return RS3_OK;
   }
@@ -430,14 +430,14 @@ rs3_status rs3_bank_create(const rs3_layer* L, int32_t cap, int32_t f_max, int32
     delete b;
     return map_err(e);
   }
-  L->n_banks++;
+  L->refs.fetch_add(1);
   *out = b;
   return RS3_OK;
 }
 
 void rs3_bank_destroy(rs3_bank* b) {
   if (!b) return;
-  if (--b->L->n_banks == 0 && b->L->destroyed) layer_free(b->L);
+  layer_release(b->L);
   BankDev& h = b->host;
   void* ptrs[] = {h.Kraw, h.Vraw, h.pos, h.Khat, h.Vhat, h.hdr, h.frames, h.tiles, b->d_desc};
   for (void* p : ptrs)
