@@ -163,9 +163,8 @@ rs3_status rs3_layer_set_rope_axial(rs3_layer* L, int32_t m, int32_t n, double t
  * destroyed, also when rs3_layer_destroy comes first; a layer and its banks may
  * be destroyed from several host threads).
  * Rows that are not finite (Inf, NaN): an evicted frame's may still reach a
- * readout where the ring keeps them in one half of a 64-key tile with resident
- * rows (fp32 layers without a workspace: in one tile), until they are
- * overwritten; anywhere else they take no part.
+ * readout where the ring keeps them in a 64-key tile that resident rows share,
+ * until they are overwritten; anywhere else they take no part.
  * Requires 0 <= n_pin < f_max <= 256, 1 <= cap <= 2^26. */
 rs3_status rs3_bank_create(const rs3_layer* L, int32_t cap, int32_t f_max,
                            int32_t n_pin, rs3_bank** out);

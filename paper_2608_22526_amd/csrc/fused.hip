@@ -84,7 +84,7 @@ hipError_t rs3_fused_setup() {
 
 // Work-groups of the fused launch beyond which the merge and the commit run
 // as two launches: a fused work-group has the commit's 1,024 threads, whose
-// register count (126) allows one per CU, while the merge's 512-thread
+// register count (127) allows one per CU, while the merge's 512-thread
 // blocks fit two per CU on their own.  Two rounds of work-groups are still
 // faster fused (eight objects on 30x54 grids, 432 work-groups: 222 against 257
 // us per six frames), four are not (eight on 64x64, 976: 357 against 340; 64

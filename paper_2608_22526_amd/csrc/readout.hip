@@ -88,9 +88,8 @@ __global__ __launch_bounds__(256) void k_qproj(Rs3ReadoutArgs a, int n_q, Rs3Cop
 }
 
 // ---------------------------------------------------------------------------
-// The attention streams the object's resident keys in 32-key half tiles
-// through nst LDS stages (nst-1 half tiles in flight; nst = 4 or 8, chosen
-// at launch with the dynamic LDS size).  One stage holds
+// The one-wave attention streams the object's resident keys in 32-key half
+// tiles through eight LDS stages.  One stage holds
 //   K : 32 rows (keys) x DH bf16, row pitch DH*2 + 16 bytes
 //   V : DH rows x 32 keys (slot order), row pitch 64 + 16 bytes
 // The pitch is an odd number of 16-byte chunks, so the 16 rows read by one
@@ -1064,20 +1063,15 @@ __global__ __launch_bounds__(CB_THREADS) void k_combine(Rs3ReadoutArgs a) {
   combine_block<OutT>(a, blockIdx.x, blockIdx.y, cl);
 }
 
-// Y[o] = X[o] (or the shared X) for every cell, converting to OutT.
+// Y[o] = X[o] (or the shared X) for every cell, converted to OutT.
 template <typename InT, typename OutT>
 __global__ __launch_bounds__(256) void k_copy_grid(const InT* X, int64_t x_stride, OutT* Y,
                                                    int64_t y_stride, int64_t count) {
   const int o = blockIdx.y;
   const InT* x = X + (int64_t)o * x_stride;
   OutT* y = Y + (int64_t)o * y_stride;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
-    if constexpr (sizeof(InT) == sizeof(OutT)) {
-      y[i] = x[i];
-    } else {
-      copy_out<OutT>(&y[i], x[i]);
-    }
-  }
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256)
+    copy_out<OutT>(&y[i], x[i]);
 }
 
 // The same for rows that keep their type.

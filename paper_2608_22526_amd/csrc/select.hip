@@ -6,9 +6,10 @@
 //            are exact in fp64, so the sums are reproducible bit for bit),
 //            and beside them the priors of small grids or the scan of the
 //            mask rows.
-// k_select : one 1024-thread workgroup per group.  Builds the group's prior
-//            bitmap in LDS (per-object bbox, streak update, separable
-//            Chebyshev dilation), then finds the k-th largest energy with an
+// k_select : one 1024-thread workgroup per group.  Takes the group's prior
+//            from that launch, or builds it as a bitmap in LDS from the scanned
+//            rows (box of each object from its rows' boxes, streak update,
+//            separable Chebyshev dilation), then finds the k-th largest energy with an
 //            MSB-first radix select over the fp64 bit patterns (energies are
 //            >= 0, so unsigned order is numeric order) and emits the kept
 //            cells in ascending order with two ordered block scans.

@@ -4,8 +4,8 @@ oracle: outputs within 2e-2 (bf16) or 1e-4 (fp32), unselected rows
 bit-identical, banks bit-exact after every fused call, for one object in
 both layer modes, eight objects with per-object lists and out-of-place
 outputs (past 768 work-groups, where the merge and the commit run as two
-launches), fp32 outputs, a rotary layer, the fp32 path (no merge launch), a frame
-with an empty selection, and forced key-split counts from 1 to 100."""
+launches), fp32 outputs, a rotary layer, fp32 layers (with the workspace of
+the tiled form, merge and commit in one launch), a frame with an empty selection, and forced key-split counts from 1 to 100."""
 from dataclasses import replace
 
 import numpy as np
@@ -49,9 +49,18 @@ def test_fused_fp32_output_and_rotary():
 
 
 def test_fused_fp32_layer_and_small_banks():
-    # the fp32 path has no merge launch: the call runs readout then commit;
     # a small ring wraps and evicts during the fused calls
-    _fused_run(CONFIGS["tiny_f32"], 8, 1)
+    import paper_2608_22526_amd as rs3
+    rs3.profile_enable(True, 256)
+    rs3.profile_reset()
+    try:
+        _fused_run(CONFIGS["tiny_f32"], 8, 1)
+        rep = rs3.profile_report()
+    finally:
+        rs3.profile_enable(False)
+    # frame 0 by rs3_commit, the seven others by the fused launch
+    assert (rep["merge_commit"][1], rep["combine"][1], rep["commit"][1]) == (7, 0, 1)
+    assert rep["readout_f32"][1] == 0
     _fused_run(replace(CONFIGS["sam2_single"], m=16, n=16, f_max=3, cap_frames=2), 9, 1, absorb=True)
 
 
