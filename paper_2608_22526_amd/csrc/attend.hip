@@ -120,12 +120,13 @@ __global__ __launch_bounds__(256) void k_attend_merge(Rs3ReadoutArgs a, int SA, 
       for (int e = 0; e < 8; ++e) acc[e] *= sc;
       M = m;
     }
-    const float w = __builtin_amdgcn_exp2f(m - M) * l;
+    float w = __builtin_amdgcn_exp2f(m - M) * part_sum(l);
     W += w;
+    w *= part_scale(l);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      acc[2 * e] += w * __uint_as_float(v[e] << 16);
-      acc[2 * e + 1] += w * __uint_as_float(v[e] & 0xffff0000u);
+      acc[2 * e] += w * part_lo<true>(v[e]);
+      acc[2 * e + 1] += w * part_hi<true>(v[e]);
     }
   }
   const float inv = W > 0.f ? 1.f / W : 0.f;

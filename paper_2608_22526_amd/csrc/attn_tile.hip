@@ -9,22 +9,26 @@
 //
 // Softmax.  The logit product starts from -m (m the lane's reference) as its
 // accumulator input, so the exponentials need no subtraction.  m is the maximum
-// of the split's first tile, and moves to a later tile's maximum when that tile
-// outweighs what came before it (SUM_RATIO below): its logits are still in
-// registers, and its weights are computed once more.  So the loop has no maximum
-// and no rescale per tile, only the test of a sum that it needs anyway.  The
-// move is for accuracy as much as for range.  A query's largest weight is then
-// exactly 1 or one of many, where against a fixed reference it is one more
-// rounded bf16 number.  Rounding error of the weights and partials, relative to
-// a reference at the maximum of half tiles that moves in steps of at least 2^8
-// (fp64 model, logits of deviation 2 to 6, 3,840 to 32,768 keys): fixed 1.02 to
-// 1.11, SUM_RATIO 0 and SUM_LOW 64 0.97 to 1.00, these 0.99 to 1.00.  On the
-// chip 4,096 queries against 28,672 keys, two heads of 128, are 0.004244 off
-// (fixed 0.004343, the half-tile form 0.004252).  A move costs about half a
-// tile, and the waves of a work-group wait for each other: that call took 126
-// us with the fixed reference and takes 137; five frames of a 128x128 grid with
-// eight heads of 32 1,606 and 1,807.
-// Whether a query's reference moves depends on that query alone.
+// of the split's first tile.  A weight 2^x above it is as good as one below (bf16
+// weights and fp32 sums have the same exponent range), so the loop needs no
+// maximum and no rescale per tile, only the test of a sum that it needs anyway:
+// where a lane's 32 weights of a tile sum to SUM_MOVE, the reference moves to
+// that tile's maximum and its weights are computed once more from the logits
+// still in registers.  Whether a query's reference moves depends on that query
+// alone.
+//
+// Precision.  Against a fixed reference a query's largest weight is one more
+// rounded number, where a reference at the maximum makes it exactly 1.  Moving
+// the reference whenever a tile outweighs those before it mends that, but costs
+// half a tile each time, on which the other waves of the work-group wait (five
+// frames of a 128x128 grid with eight heads of 32: 1,837 instead of 1,626 us).
+// The larger error is that of the partials in bf16, so they are f16 at a scale of
+// the row's own instead (part_sum in device_util.h).  Rounding error of weights
+// and partials, relative to a reference moved per half tile in steps of at least
+// 2^8 with bf16 partials (fp64 model, logits of deviation 2 to 6, 3,840 to 32,768
+// keys): this form 0.43 to 0.68, with bf16 partials 1.02 to 1.10.  On the chip,
+// 4,096 queries against 28,672 keys, two heads of 128: 0.00402 off here, the
+// half-tile form 0.00425, the fixed reference with bf16 partials 0.00434.
 //
 // What bounds it: instruction issue.  Measured per SIMD (cycles at 2.4 GHz,
 // four waves): v_exp_f32 8.7, other VALU 5.6, a 32x32x16 MFMA 35; one wave
@@ -50,9 +54,9 @@
 
 namespace rs3 {
 
-// The reference moves for a tile whose 32 weights in a lane sum to SUM_RATIO
-// times all before them, at least SUM_LOW and at most SUM_HIGH.
-constexpr float SUM_RATIO = 1.5f, SUM_LOW = 128.f, SUM_HIGH = 1024.f;
+// Sum of a lane's 32 weights of a tile from which on the reference moves.
+constexpr float SUM_MOVE = 0x1p20f;
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 template <int DH>
 struct TileLds {
@@ -213,12 +217,15 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
         for (int r = 0; r < 16; ++r) sc[kh][r] = m >> (8 * (r >> 2) + (r & 3)) & 1u ? sc[kh][r] : -INFINITY;
         // a half without resident rows may hold values that are no numbers,
         // which a weight of 0 does not hide: each wave clears its V^ for itself
-        // (all write the same; a branch in the product took 9 % of its time)
-        if (mk[kh] == 0u)
-          for (int i = lane; i < DH * 4; i += 64) {
+        // (all write the same; a branch in the product took up to 9 %)
+        if (mk[kh] == 0u) {
+          int l = lane;
+          asm volatile("" : "+v"(l));   // the addresses are not worth registers across the loop
+          for (int i = l; i < DH * 4; i += 64) {
             const int d = i >> 2, c = 4 * kh + (i & 3);
             *(u32x4*)(st + L::VOFF + d * 128 + ((c ^ L::fv(d)) << 4)) = u32x4{0, 0, 0, 0};
           }
+        }
       }
     }
     // weights against the reference, and their sum over this lane's keys
@@ -237,7 +244,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
       ts = t[0] + t[1];
     };
     if (j > 0) weights(BIAS ? 0.f : m_run);
-    const bool hit = unseen || !(ts < __builtin_amdgcn_fmed3f(SUM_RATIO * l_run, SUM_LOW, SUM_HIGH));   // also for NaN
+    const bool hit = unseen || !(ts < SUM_MOVE);   // also for NaN
     if (__any(hit)) {
       // the reference of the queries whose sum asks for it moves to the tile's
       // maximum, and so does that of the unseen ones (all of them on the first
@@ -271,30 +278,59 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
   }
   l_run = sum_with_partner(l_run);
   __syncthreads();   // the stages are free
-  // Epilogue: this wave's normalised rows through LDS as [query][d] bf16,
-  // then whole rows in 16-byte stores.
+  // Epilogue: this wave's normalised rows through LDS as [query][d] f16 at the
+  // row's scale, then whole rows in 16-byte stores.
   constexpr int OP = DH * 2 + 16;
   static_assert(NW * 32 * OP <= NST * L::STAGE, "the rows fit the stages");
   uint8_t* ow = lds + wave * 32 * OP;
   const float inv = l_run > 0.f ? __builtin_amdgcn_rcpf(l_run) : 0.f;
+  // the row's largest magnitude among its finite values (at 256 channels, one
+  // wave per SIMD, the test of each is left to rows that need it: 1.5 us)
+  float big = 0.f;
+  if constexpr (DH > 128) {
+    float b4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2)
+        b4[r / 2 & 3] = max3f(b4[r / 2 & 3], __builtin_fabsf(acc[dt][r]), __builtin_fabsf(acc[dt][r + 1]));
+    big = max3f(__builtin_elementwise_maximum(b4[0], b4[1]), b4[2], b4[3]);
+  }
+  if (DH <= 128 || __any(!(big < INFINITY))) {
+    big = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float x = __builtin_fabsf(acc[dt][r]);
+        big = x < INFINITY ? fmaxf(big, x) : big;
+      }
+  }
+  const int e = max(__builtin_amdgcn_frexp_expf(max_with_partner(big) * inv) - 15, -126);   // row / 2^e < 2^15
+  const float f = __builtin_amdgcn_ldexpf(inv, -e);
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
-      u32x2 w;
-      w[0] = pack_bf16x2(acc[dt][4 * q4] * inv, acc[dt][4 * q4 + 1] * inv);
-      w[1] = pack_bf16x2(acc[dt][4 * q4 + 2] * inv, acc[dt][4 * q4 + 3] * inv);
-      *(u32x2*)(ow + l31 * OP + (32 * dt + 8 * q4 + 4 * g) * 2) = w;
+      f16x4 w;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[r] = (_Float16)(acc[dt][4 * q4 + r] * f);
+      *(f16x4*)(ow + l31 * OP + (32 * dt + 8 * q4 + 4 * g) * 2) = w;
     }
   if (g == 0 && row < cnt) {
     float* p = ml + (int64_t)row * H * 2;
-    const float m = unseen ? -INFINITY : m_run;
+    float m = unseen ? -INFINITY : m_run, lo = l_run;
+    if (l_run > 0.f) {   // (device_util.h, at part_sum)
+      const int el = __builtin_amdgcn_frexp_expf(l_run) - 1;
+      m += (float)el;
+      lo = __builtin_amdgcn_ldexpf(l_run, e - el);
+    }
     if (a.stream_parts) {
       pstore(p, m);
-      pstore(p + 1, l_run);
+      pstore(p + 1, lo);
     } else {
       p[0] = m;
-      p[1] = l_run;
+      p[1] = lo;
     }
   }
   // the staged rows of a wave are written and read by that wave alone

@@ -82,6 +82,7 @@ __device__ __forceinline__ void part_load(const Rs3ReadoutArgs& a, int o, int ro
 // rescaled once per batch instead of once per split.  Splits that are off
 // (past S, or empty with l = 0) add nothing; their partial O words are
 // replaced by zero before use, since an empty split leaves its O unwritten.
+template <bool F16>
 __device__ __forceinline__ void part_merge(const PartBatch& pb, int first, int NG, int S, float& M, float& W,
                                            float (&acc)[8]) {
   bool on[PART_B];
@@ -99,21 +100,23 @@ __device__ __forceinline__ void part_merge(const PartBatch& pb, int first, int N
   for (int e = 0; e < 8; ++e) acc[e] *= sc;
 #pragma unroll
   for (int i = 0; i < PART_B; ++i) {
-    const float w = on[i] ? __builtin_amdgcn_exp2f(pb.m[i] - Mn) * pb.l[i] : 0.f;
+    float w = on[i] ? __builtin_amdgcn_exp2f(pb.m[i] - Mn) * (F16 ? part_sum(pb.l[i]) : pb.l[i]) : 0.f;
     W += w;
+    if constexpr (F16) w = on[i] ? w * part_scale(pb.l[i]) : 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const uint32_t x = on[i] ? pb.v[i][e] : 0u;
-      acc[2 * e] += w * __uint_as_float(x << 16);
-      acc[2 * e + 1] += w * __uint_as_float(x & 0xffff0000u);
+      acc[2 * e] += w * part_lo<F16>(x);
+      acc[2 * e + 1] += w * part_hi<F16>(x);
     }
   }
   M = Mn;
 }
 
 // The merge of rows [ry*RB, +RB) of object o, RB = cb_rows_for(D, n_obj, max_sel), by CB_THREADS threads
-// (threadIdx.x < CB_THREADS), cl: combine_lds_bytes(D) bytes of LDS.
-template <typename OutT>
+// (threadIdx.x < CB_THREADS), cl: combine_lds_bytes(D) bytes of LDS.  F16: the
+// partials are the tiled attention's.
+template <typename OutT, bool F16>
 __device__ __forceinline__ void combine_block(const Rs3ReadoutArgs& a, int o, int ry, uint8_t* cl) {
   const int RB = cb_rows_for(a.D, a.n_obj, a.max_sel);
   const int r0 = ry * RB;
@@ -195,7 +198,7 @@ __device__ __forceinline__ void combine_block(const Rs3ReadoutArgs& a, int o, in
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int j = 0; j < nb; ++j) {
       if (q != q0 || j > 0) part_load(a, o, r0 + rr, d0, h, grp, NG, j, pb);
-      part_merge(pb, grp + NG * PART_B * j, NG, S, M, W, acc);
+      part_merge<F16>(pb, grp + NG * PART_B * j, NG, S, M, W, acc);
     }
     float* dstp = red + (size_t)grp * 10 * items + item;   // [NG][10][items]
     dstp[0] = M;

@@ -127,6 +127,30 @@ __device__ __forceinline__ f32x16 mfma32f(const f32x4& a, const f32x4& b, f32x16
   return c;
 }
 
+// Partials of the tiled attention (k_attn_tile), per row, head and split: the
+// normalised O as f16 times a power of two of the row's own, (m, l) as two
+// floats.  l is brought to [1, 2) and its exponent added to m, which leaves
+// the exponent field of the second float for the scale: 2^e of O, e that of the
+// row's largest value less 14, so that f16 has its 11 bits down to 2^-28 of
+// it.  Not above 0 (empty, or no number): nothing to decode.  The one-wave
+// attention stores O as bf16 and l as it is.
+__device__ __forceinline__ float part_sum(float l) {   // l in [1, 2)
+  return __uint_as_float((__float_as_uint(l) & 0x007fffffu) | 0x3f800000u);
+}
+__device__ __forceinline__ float part_scale(float l) { return __uint_as_float(__float_as_uint(l) & 0x7f800000u); }
+
+// The two values of a word of partial O.
+template <bool F16>
+__device__ __forceinline__ float part_lo(uint32_t x) {
+  if constexpr (F16) return (float)__builtin_bit_cast(_Float16, (uint16_t)(x & 0xffffu));
+  return __uint_as_float(x << 16);
+}
+template <bool F16>
+__device__ __forceinline__ float part_hi(uint32_t x) {
+  if constexpr (F16) return (float)__builtin_bit_cast(_Float16, (uint16_t)(x >> 16));
+  return __uint_as_float(x & 0xffff0000u);
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dppf(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));

@@ -22,7 +22,7 @@ namespace rs3 {
 // launches), are loaded in one batch at the start (one memory round trip),
 // so that the later loads behind the block-kind test and the table index
 // find them in the scalar cache.
-template <typename OutT, bool BF16>
+template <typename OutT, bool F16>
 __global__ __launch_bounds__(CP_THREADS) void k_merge_commit(Rs3ReadoutArgs ra, Rs3CommitArgs ca, int n_cb) {
   extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
   asm volatile("" ::"s"(n_cb), "s"(ra.n_obj), "s"(ra.D), "s"(ra.max_sel), "s"(ra.sel_idx), "s"(ra.sel_stride),
@@ -32,10 +32,10 @@ __global__ __launch_bounds__(CP_THREADS) void k_merge_commit(Rs3ReadoutArgs ra, 
   const int b = blockIdx.x;
   if (b < n_cb) {
     if (threadIdx.x >= CB_THREADS) return;
-    combine_block<OutT>(ra, b % ra.n_obj, b / ra.n_obj, dyn);
+    combine_block<OutT, F16>(ra, b % ra.n_obj, b / ra.n_obj, dyn);
   } else {
     const int c = b - n_cb;
-    commit_block<BF16>(ca, c % ca.n_obj, c / ca.n_obj, (int32_t*)dyn);
+    commit_block<true>(ca, c % ca.n_obj, c / ca.n_obj, (int32_t*)dyn);
   }
 }
 
@@ -73,7 +73,8 @@ hipError_t rs3_fused_setup() {
     const size_t b = merge_commit_lds(D, 256);
     if (b > max_lds) max_lds = b;
   }
-  const void* fs[] = {(const void*)k_merge_commit<bf16_t, true>, (const void*)k_merge_commit<float, true>};
+  const void* fs[] = {(const void*)k_merge_commit<bf16_t, false>, (const void*)k_merge_commit<bf16_t, true>,
+                      (const void*)k_merge_commit<float, false>, (const void*)k_merge_commit<float, true>};
   for (const void* f : fs) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
     if (e != hipSuccess) return e;
@@ -110,9 +111,14 @@ hipError_t rs3_launch_merge_commit(const Rs3ReadoutArgs& ra, const Rs3CommitArgs
   }
   const size_t lds = merge_commit_lds(ra.D, d_kv);
   const dim3 grid(n_cb + n_cp), blk(CP_THREADS);
-  if (ra.y_fp32)
+  const bool f16 = !rs3_attn_projects(ra);   // the form that wrote the partials
+  if (ra.y_fp32 && f16)
     RS3_LAUNCH(RS3_K_MERGE_COMMIT, st, (k_merge_commit<float, true>), grid, blk, lds, st, ra, c, n_cb);
-  else
+  else if (ra.y_fp32)
+    RS3_LAUNCH(RS3_K_MERGE_COMMIT, st, (k_merge_commit<float, false>), grid, blk, lds, st, ra, c, n_cb);
+  else if (f16)
     RS3_LAUNCH(RS3_K_MERGE_COMMIT, st, (k_merge_commit<bf16_t, true>), grid, blk, lds, st, ra, c, n_cb);
+  else
+    RS3_LAUNCH(RS3_K_MERGE_COMMIT, st, (k_merge_commit<bf16_t, false>), grid, blk, lds, st, ra, c, n_cb);
   return hipGetLastError();
 }

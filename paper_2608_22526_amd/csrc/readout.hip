@@ -1057,10 +1057,10 @@ __global__ __launch_bounds__(512) void k_attn_g2(Rs3ReadoutArgs a, int G, Rs3Att
 
 // ---------------------------------------------------------------------------
 // grid (n_obj, ceil(max_sel/cb_rows_for(D, n_obj, max_sel))), block CB_THREADS: one merge block each.
-template <typename OutT>
+template <typename OutT, bool F16>
 __global__ __launch_bounds__(CB_THREADS) void k_combine(Rs3ReadoutArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t cl[];
-  combine_block<OutT>(a, blockIdx.x, blockIdx.y, cl);
+  combine_block<OutT, F16>(a, blockIdx.x, blockIdx.y, cl);
 }
 
 // Y[o] = X[o] (or the shared X) for every cell, converted to OutT.
@@ -1184,10 +1184,15 @@ hipError_t rs3_launch_combine(const Rs3ReadoutArgs& a, hipStream_t st) {
   const size_t lds = combine_lds_bytes(a.D);
   const int rb = cb_rows_for(a.D, a.n_obj, a.max_sel);
   const dim3 cgrid(a.n_obj, (a.max_sel + rb - 1) / rb);
-  if (a.y_fp32)
-    RS3_LAUNCH(RS3_K_COMBINE, st, k_combine<float>, cgrid, dim3(CB_THREADS), lds, st, a);
+  const bool f16 = !attn_projects(a);   // the form that wrote the partials
+  if (a.y_fp32 && f16)
+    RS3_LAUNCH(RS3_K_COMBINE, st, (k_combine<float, true>), cgrid, dim3(CB_THREADS), lds, st, a);
+  else if (a.y_fp32)
+    RS3_LAUNCH(RS3_K_COMBINE, st, (k_combine<float, false>), cgrid, dim3(CB_THREADS), lds, st, a);
+  else if (f16)
+    RS3_LAUNCH(RS3_K_COMBINE, st, (k_combine<bf16_t, true>), cgrid, dim3(CB_THREADS), lds, st, a);
   else
-    RS3_LAUNCH(RS3_K_COMBINE, st, k_combine<bf16_t>, cgrid, dim3(CB_THREADS), lds, st, a);
+    RS3_LAUNCH(RS3_K_COMBINE, st, (k_combine<bf16_t, false>), cgrid, dim3(CB_THREADS), lds, st, a);
   return hipGetLastError();
 }
 
@@ -1198,20 +1203,21 @@ hipError_t rs3_readout_setup() {
     const size_t b = combine_lds_bytes(D);
     if (b > max_lds) max_lds = b;
   }
-  hipError_t e = hipFuncSetAttribute((const void*)k_combine<bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)max_lds);
-  if (e != hipSuccess) return e;
   const struct {
     const void* f;
     int bytes;
-  } attn[] = {{(const void*)k_attn<32>, ATTN32_LDS},
-              {(const void*)k_attn_g2<false, false>, G2Lds::BYTES},
-              {(const void*)k_attn_g2<false, true>, G2Lds::BYTES},
-              {(const void*)k_attn_g2<true, false>, 8 * G2Lds::STAGE},
-              {(const void*)k_attn_g2<true, true>, 8 * G2Lds::STAGE}};
-  for (const auto& k : attn) {
-    e = hipFuncSetAttribute(k.f, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
+  } ks[] = {{(const void*)k_combine<bf16_t, false>, (int)max_lds},
+            {(const void*)k_combine<bf16_t, true>, (int)max_lds},
+            {(const void*)k_combine<float, false>, (int)max_lds},
+            {(const void*)k_combine<float, true>, (int)max_lds},
+            {(const void*)k_attn<32>, ATTN32_LDS},
+            {(const void*)k_attn_g2<false, false>, G2Lds::BYTES},
+            {(const void*)k_attn_g2<false, true>, G2Lds::BYTES},
+            {(const void*)k_attn_g2<true, false>, 8 * G2Lds::STAGE},
+            {(const void*)k_attn_g2<true, true>, 8 * G2Lds::STAGE}};
+  for (const auto& k : ks) {
+    hipError_t e = hipFuncSetAttribute(k.f, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
     if (e != hipSuccess) return e;
   }
-  return hipFuncSetAttribute((const void*)k_combine<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
+  return hipSuccess;
 }

@@ -226,7 +226,7 @@ struct Rs3ReadoutArgs {
   const void* WqT;        // [D][C]
   const void* WoT;        // [C][D]
   void* Q;                // [n_obj][max_sel][D] workspace in the layer's dtype (fp32 layers: null = direct form)
-  void* Opart;            // [n_obj][S][max_sel][D] workspace in the layer's dtype
+  void* Opart;            // [n_obj][S][max_sel][D] workspace: fp32; bf16 layers: f16 (k_attn_tile) or bf16
   float* ML;              // [n_obj][S][max_sel][H][2] workspace
   float qscale;           // log2(e) / sqrt(d_h)
   int mn, C, H, d_h, D, n_obj, max_sel, S, n_qt, y_fp32;   // n_qt: query tiles (128 rows, fp32 layers 32)

@@ -82,7 +82,7 @@ __device__ __forceinline__ int stk_cell(const StkArgs& p, int r) {
 
 // ---- prologues: the A chunk [64][kn] of rows row0.. in LDS (bf16) ----------
 // grid ceil(M*D_att/8 / 256), block 256: one thread per (kept row, 8 columns)
-// merges the attention's key splits (partials O/l and (m, l) per split, row
+// merges the attention's key splits (k_attn_tile's partials per split, row
 // and head: Opart [S][M][D_att], ML [S][M][H_att][2]) by log-sum-exp into the
 // normalised bf16 rows mout [M][D_att].  The splits are loaded eight at a time
 // without branches (split indices past S re-read the last split and are
@@ -122,13 +122,14 @@ __global__ __launch_bounds__(256) void k_stk_merge(StkArgs p) {
     for (int e = 0; e < 8; ++e) acc[e] *= sc;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float w = on[i] ? __builtin_amdgcn_exp2f(ml[i][0] - Mn) * ml[i][1] : 0.f;
+      float w = on[i] ? __builtin_amdgcn_exp2f(ml[i][0] - Mn) * part_sum(ml[i][1]) : 0.f;
       W += w;
+      w = on[i] ? w * part_scale(ml[i][1]) : 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const uint32_t x = on[i] ? v[i][e] : 0u;
-        acc[2 * e] += w * __uint_as_float(x << 16);
-        acc[2 * e + 1] += w * __uint_as_float(x & 0xffff0000u);
+        acc[2 * e] += w * part_lo<true>(x);
+        acc[2 * e + 1] += w * part_hi<true>(x);
       }
     }
     M = Mn;
