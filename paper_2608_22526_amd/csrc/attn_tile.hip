@@ -228,6 +228,13 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
         }
       }
     }
+    // The first value operands in flight during the weights, whose test keeps the
+    // compiler from loading them there: 350 -> 345 us per six frames with a head
+    // of 256, 127 -> 125 at two heads of 128; at 64 their registers cost more.
+    constexpr int NP = DH <= 32 ? 1 : DH <= 64 ? 0 : 4;
+    u32x4 vp[4];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) vp[i] = *(const u32x4*)(st + va[i]);
     // weights against the reference, and their sum over this lane's keys
     u32x4 pk[4];
     float ts = 0.f;
@@ -271,7 +278,12 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 ? 4 : DH <= 64 ? 3 : DH <= 128 ? 
     for (int dt = 0; dt < NDT; ++dt) {
       u32x4 vf[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) vf[i] = *(const u32x4*)(st + va[i] + dt * 32 * 128);
+      for (int i = 0; i < 4; ++i) {
+        if (dt == 0 && i < NP)
+          vf[i] = vp[i];
+        else
+          vf[i] = *(const u32x4*)(st + va[i] + dt * 32 * 128);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[dt] = mfma32(vf[i], pk[i], acc[dt]);
     }
