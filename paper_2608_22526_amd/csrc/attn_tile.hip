@@ -37,11 +37,10 @@
 // 510 cycles) beside 8 MFMAs (280) at d_h = 32, 32 (1,120) at 128.  So the
 // form keeps the registers of one query tile per wave (four, three and two
 // waves per SIMD at d_h = 32, 64 and 128).  Measured, against the half-tile
-// form: 128x128 grid, eight heads of 32, 16 frames 634 -> 437 us; 64 objects,
-// one head of 64 160 -> 98 us; 42 k keys, one head of 64 52 -> 36 us; 4,096
-// queries, 28,672 keys, two heads of 128 207 -> 110 us (1.1 PFLOP/s, where a
-// large matrix product reaches 1.24 on this chip); 900 queries, 6.7 k keys, one
-// head of 256 25 -> 21 us.  Tried on one machine, slower: two query tiles per
+// form: 128x128 grid, eight heads of 32, 16 frames 648 -> 453 us; 64 objects,
+// one head of 64 160 -> 102 us; 4,096 queries, 28,672 keys, two heads of 128 236
+// -> 125 us (0.96 PFLOP/s, where a large matrix product reaches 1.24 on this
+// chip); 900 queries, 6.7 k keys, one head of 256 25 -> 21 us.  Tried on one machine, slower: two query tiles per
 // wave (two waves per SIMD at d_h = 32 and 64: 24 % and 22 %), the row sums as
 // a product with ones (5 %), the halves one after the other (0-5 %).
 //
@@ -378,7 +377,8 @@ static hipError_t launch(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStr
 
 // Three stages, four waves; at d_h = 128 eight waves, since a stage is 32 KB
 // and two work-groups of four with two stages each keep less in flight (110
-// against 116 us at the sizes above); at 256 two stages fill the LDS.
+// against 116 us at the sizes above, with bf16 partials); at 256 two stages
+// fill the LDS.
 hipError_t rs3_launch_attn_tile(const Rs3ReadoutArgs& a, const Rs3AttnBanks& ab, hipStream_t st) {
   switch (a.d_h) {
     case 32: return launch<32, 4, 3>(a, ab, st);
