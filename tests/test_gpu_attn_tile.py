@@ -39,7 +39,8 @@ def _rand(rng, *shape, scale=1.0):
 
 
 @pytest.mark.parametrize("d_h,H", [(32, 8), (64, 3), (128, 2), (256, 1)])
-@pytest.mark.parametrize("n_q,n_kv,n_splits", [(1, 1, 0), (33, 63, 0), (129, 65, 2), (300, 4200, 1), (257, 4097, 5)])
+@pytest.mark.parametrize("n_q,n_kv,n_splits", [(1, 1, 0), (33, 63, 0), (129, 65, 2), (300, 4200, 1), (257, 4097, 5),
+                                              (100, 9000, 0)])   # waves without rows at heads of 128
 def test_tile_edges(d_h, H, n_q, n_kv, n_splits):
     rng = np.random.default_rng(d_h + n_q + n_kv)
     got, ref = _attend(_rand(rng, n_q, H, d_h, scale=2.0), _rand(rng, n_kv, H, d_h), _rand(rng, n_kv, H, d_h), n_splits)
