@@ -40,9 +40,10 @@
 // form: 128x128 grid, eight heads of 32, 16 frames 648 -> 453 us; 64 objects,
 // one head of 64 160 -> 102 us; 4,096 queries, 28,672 keys, two heads of 128 236
 // -> 125 us (0.96 PFLOP/s, where a large matrix product reaches 1.24 on this
-// chip); 900 queries, 6.7 k keys, one head of 256 25 -> 21 us.  Tried on one machine, slower: two query tiles per
-// wave (two waves per SIMD at d_h = 32 and 64: 24 % and 22 %), the row sums as
-// a product with ones (5 %), the halves one after the other (0-5 %).
+// chip); 900 queries, 6.7 k keys, one head of 256 25 -> 21 us.  Tried on one
+// machine, slower: two query tiles per wave (two waves per SIMD at d_h = 32 and
+// 64: 24 % and 22 %), the row sums as a product with ones (5 %), the halves one
+// after the other (0-5 %).
 //
 // LDS: NST stages of one tile, K^ as 64 rows (keys) x DH and V^ as DH rows x
 // 64 keys (slot order), without padding: 16-byte chunk c of row r lies at
